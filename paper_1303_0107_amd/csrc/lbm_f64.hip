@@ -75,6 +75,32 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], int tid) {
         for (int k = 0; k < NV; ++k) v[k] = ((red[0][k] + red[1][k]) + red[2][k]) + red[3][k];
 }
 
+// a / r and b / r, rounded as the divisions round them, with one reciprocal:
+// Newton steps bring the hardware estimate of 1/r within an ulp, and one
+// exact-remainder correction then rounds each quotient correctly (Markstein,
+// IBM J. Res. Dev. 34, 1990).  Where r is far from 1 the remainder or the
+// reciprocal could leave the normal range, so those waves divide.  A quotient
+// below 2^-500 may differ in its last place; it is lost entirely in the sums
+// 1 + 3 c.u and in the squares it enters.  Eleven instructions for the pair,
+// the two divisions take 22.
+__device__ __forceinline__ void divide_pair(double a, double b, double r, double &qa,
+                                            double &qb) {
+    // biased exponent of r within 512 of that of 1, and r positive
+    const uint32_t hi = (uint32_t)((uint64_t)__double_as_longlong(r) >> 32);
+    if (__builtin_expect(__any(hi - (511u << 20) >= (1024u << 20)), 0)) {
+        qa = a / r;
+        qb = b / r;
+        return;
+    }
+    double y = __builtin_amdgcn_rcp(r);
+    y = __builtin_fma(__builtin_fma(-r, y, 1.0), y, y);
+    y = __builtin_fma(__builtin_fma(-r, y, 1.0), y, y);
+    qa = a * y;
+    qb = b * y;
+    qa = __builtin_fma(__builtin_fma(-r, qa, a), y, qa);
+    qb = __builtin_fma(__builtin_fma(-r, qb, b), y, qb);
+}
+
 // One cell of one time step on full populations: Zou-He closure on inlet
 // (velocity u_in, unknowns 1, 5, 8) and outlet cells (density rho_out, zero
 // transverse velocity, unknowns 3, 6, 7), moments (Eq. 2), relaxation
@@ -116,19 +142,31 @@ struct Cell {
             f[7] = f[5] + 0.5 * (f[2] - f[4]) - (1.0 / 6.0) * ru - 0.5 * rv;
             f[6] = f[8] - 0.5 * (f[2] - f[4]) - (1.0 / 6.0) * ru + 0.5 * rv;
         }
-        double r, mx, my;
-        moments(f, r, mx, my);
-        ux = mx / r;
-        uy = my / r;
-        const double uu = ux * ux + uy * uy;
-        const double om = a.omega;
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            const double cu = kCx[i] * ux + kCy[i] * uy;
-            const double feq =
-                weight(i) * r * (1.0 + cu * 3.0 + 0.5 * (cu * cu) * 9.0 - 0.5 * uu * 3.0);
-            f[i] = f[i] - om * (f[i] - feq);
-        }
+        // Moments and relaxation in the definition's order, without the
+        // operations that cannot change a result: terms with a zero velocity
+        // component are left out, opposite populations share 3 c.u and
+        // 4.5 (c.u)^2 (their c.u differ in sign alone), and 0.5 x 9 and
+        // 0.5 x 3 are one product (halving is exact).  Every population keeps
+        // the bits of the expressions as the definition writes them.  With
+        // the shared reciprocal 117 vector instructions a cell in place of
+        // 205; 1024 x 512 distributor, 4000 steps: 15.2 -> 13.0 ms (in-place
+        // regions, whose pulls also lost their address arithmetic).
+        const double r = f[0] + f[1] + f[2] + f[3] + f[4] + f[5] + f[6] + f[7] + f[8];
+        const double mx = f[1] - f[3] + f[5] - f[6] - f[7] + f[8];
+        const double my = f[2] - f[4] + f[5] + f[6] - f[7] - f[8];
+        divide_pair(mx, my, r, ux, uy);
+        const double v = 1.5 * (ux * ux + uy * uy), om = a.omega;
+        const double w0 = weight(0) * r, w1 = weight(1) * r, w5 = weight(5) * r;
+        f[0] = f[0] - om * (f[0] - w0 * (1.0 - v));
+        auto relax_pair = [&](int i, int j, double cu, double w) {  // c_j = -c_i
+            const double c3 = cu * 3.0, s = 4.5 * (cu * cu);
+            f[i] = f[i] - om * (f[i] - w * (1.0 + c3 + s - v));
+            f[j] = f[j] - om * (f[j] - w * (1.0 - c3 + s - v));
+        };
+        relax_pair(1, 3, ux, w1);
+        relax_pair(2, 4, uy, w1);
+        relax_pair(5, 7, ux + uy, w5);
+        relax_pair(8, 6, ux - uy, w5);
         mass = r;
     }
 };
