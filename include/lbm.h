@@ -365,7 +365,10 @@ int lbm_set_tb_variant(lbm_handle *h, int32_t variant);
  * or lbm_autotune choice, or, after an exchange step pushed the autotuned
  * shape's active tiles past one round of workgroups, the fastest timed shape
  * whose tiles still fit (the autotuned shape is taken back once it fits
- * again).  -1 when temporal blocking is off (one launch per step).
+ * again).  -1 when temporal blocking is off (one launch per step).  A large
+ * lattice that is mostly fluid may be advanced without regions (the marching
+ * sweep) until a shape is set; the shape named here is then the one of its
+ * blocked sweeps.
  * Errors: LBM_EINVAL (NULL argument). */
 int lbm_get_tb_variant(lbm_handle *h, int32_t *variant);
 

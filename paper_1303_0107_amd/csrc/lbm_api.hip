@@ -385,6 +385,9 @@ struct lbm_handle {
     int cus = 0;
     size_t lds_per_cu = 0;
     uint64_t mask_version = 0;  // bumped whenever the mask changes
+    int march = 0;              // steps per launch of the marching sweep, 0: blocked sweep
+    int march_env = -1;         // LBM_MARCH: 0 never, n >= 1 steps wherever possible, -1 unset
+    int64_t check_parts = 0;    // partials of the last check launch
     // Non-solid cell counts per tile of a tw x th tiling and the tiles that
     // hold one, row-major, packed (tile row << 16 | tile column); built once
     // per tiling by a scan of the mask, then kept current from the cells each
@@ -705,6 +708,75 @@ MacroArgs<T> macro_args(lbm_handle *h) {
     return a;
 }
 
+// Lattices of at least this many cells march untuned: below, a segment has too
+// few rows for what it advances beyond its ends.  us per step against the
+// best region shape, all-fluid channels, FP32: 1024 x 512 4.6 against 4.0,
+// 1400 x 700 5.9 against 6.3, 1700 x 850 6.8 against 8.4, 2300 x 2000 15.6
+// against 29.3; FP16: 1400 x 700 6.7 against 6.8, 2300 x 2000 18.6 against
+// 27.6; FP64: 700 x 350 6.1 against 5.3, 1024 x 512 7.7 against 8.2, 1400 x
+// 700 10.5 against 14.9, 2300 x 2000 50 against 62.  The autotuner times both
+// from kMarchTuneCells on.
+constexpr int64_t kMarchCells = 900000, kMarchCells64 = (int64_t)1 << 19,
+                  kMarchTuneCells = (int64_t)1 << 19;
+
+// Whether the marching sweep (lbm_march.h) can run on a lattice: it has no
+// boundary-variant paths and needs two strips.
+bool can_march(const lbm_handle *h) { return h->use_tb && h->flags == 0 && h->nx >= 128; }
+
+// Whether it is considered: it advances solid cells too, the blocked sweep
+// skips tiles without fluid, so only on lattices that are mostly fluid.
+bool may_march(const lbm_handle *h) {
+    return can_march(h) && h->march_env != 0 && 4 * h->n_nonsolid >= 3 * (int64_t)h->N();
+}
+
+// Steps of a marching launch.  In double the registers end at 4; otherwise 6,
+// or 7 on the largest lattices, which HBM bounds (us per step with 4, 6 and 7:
+// 1700 x 850 FP32 8.2, 6.8, 7.0; 2300 x 2000 FP32 24.4, 17.6, 15.6; FP16 20.5,
+// 18.6, 18.9).  Eight spill.
+int march_steps(const lbm_handle *h) {
+    if (h->march_env > 0) return std::min(h->march_env, h->precision == LBM_F64 ? 4 : 7);
+    return h->precision == LBM_F64 ? 4 : h->N() < (size_t)4 << 20 ? 6 : 7;
+}
+
+// Steps per launch before (or without) the autotuner; 0: the blocked sweep.
+int default_march(const lbm_handle *h) {
+    const int64_t from = h->precision == LBM_F64 ? kMarchCells64 : kMarchCells;
+    const bool on = h->march_env > 0 ? can_march(h) : may_march(h) && (int64_t)h->N() >= from;
+    return on ? march_steps(h) : 0;
+}
+
+// Segments of a marching launch: the shortest (at least four rows) for which
+// all workgroups run at once with `fill` waves on each SIMD.  Fewer waves do
+// not hide the latency of their own instructions, more only lengthen the
+// launch by the rows that each segment advances beyond its ends.  us per
+// step with 1, 2 and 3: 4096 x 2048 FP32, 7 steps, 33.6, 29.6, 32.3; 2000 x
+// 1000 FP32, 6 steps, 10.5 (7 steps), 7.9, 8.5; 2000 x 1000 FP16, 4 steps,
+// 9.3 with 3 and 9.8 with 4.
+MarchPlan march_plan(const lbm_handle *h, int steps) {
+    const int fill = steps <= 4 && h->precision != LBM_F64 ? 3 : 2;
+    const int target = fill * h->cus * (kMarchThreads / 64);
+    const int iw = 64 - 2 * steps;
+    MarchPlan p{};
+    p.steps = steps;
+    p.strips = (h->nx + iw - 1) / iw;
+    for (p.rows = std::max(4, (int)((int64_t)h->ny * p.strips / target));; ++p.rows) {
+        p.segs = (h->ny + p.rows - 1) / p.rows;
+        p.edge_rows = (p.rows + 1) / 2;
+        p.edge_segs = (h->ny + p.edge_rows - 1) / p.edge_rows;
+        p.waves = 2 * p.edge_segs + (p.strips - 2) * p.segs;
+        if (p.waves <= target || p.rows >= h->ny) break;
+    }
+    p.blocks = (p.waves + kMarchThreads / 64 - 1) / (kMarchThreads / 64);
+    return p;
+}
+
+// Steps of the next marching launch when n are left.
+int march_next(const lbm_handle *h, int64_t n) {
+    for (int s : {7, 6, 4, 2})
+        if (s <= h->march && s <= n) return s;
+    return 1;
+}
+
 template <typename T>
 void step(lbm_handle *h, bool check) {
     HIP_TRY(launch_sweep<T>(sweep_args<T>(h, check), check, h->stream));
@@ -758,9 +830,24 @@ void plain_sweeps(lbm_handle *h, int64_t n) {
 }
 
 // Advance `n` >= 1 steps; with `check` the last step also writes residual
-// partials (per tile or per sweep block; see partial_count).
+// partials (per tile, sweep block or marching workgroup: check_parts).
 template <typename T>
 void advance(lbm_handle *h, int64_t n, bool check) {
+    if (h->march) {
+        while (n > 0) {
+            const MarchPlan p = march_plan(h, march_next(h, n));
+            n -= p.steps;
+            if (check && n == 0 && (size_t)p.blocks * 4 * sizeof(double) > h->partials.bytes)
+                throw HipFail{hipErrorInvalidValue, "partials of a marching check launch"};
+            HIP_TRY(launch_march<T>(sweep_args<T>(h, check && n == 0), p, check && n == 0,
+                                    h->stream));
+            h->cur = 1 - h->cur;
+            h->check_parts = p.blocks;
+            ++h->prof_kernels;
+        }
+        return;
+    }
+    h->check_parts = h->use_tb ? h->n_tiles : sweep_blocks(h->nx, h->ny);
     if (h->use_tb) {
         bool first = true;
         while (n > 0) {
@@ -794,10 +881,6 @@ void advance(lbm_handle *h, int64_t n, bool check) {
     }
 }
 
-int64_t partial_count(const lbm_handle *h) {
-    return h->use_tb ? h->n_tiles : sweep_blocks(h->nx, h->ny);
-}
-
 template <typename T>
 void uprev_from_state(lbm_handle *h) {
     MacroArgs<T> a = macro_args<T>(h);
@@ -829,7 +912,6 @@ int run_impl(lbm_handle *h, int64_t max_steps, double tol, int32_t k,
              int64_t *steps_done, double *residual) {
     ensure_pinned(h, sizeof(RunControl));
     uprev_from_state<T>(h);
-    const int64_t nparts = partial_count(h);
     // Check intervals are queued several at a time (temporal blocking only):
     // each interval's finalize step decides on the device whether the run
     // goes on, the launches queued after the deciding one change nothing, and
@@ -853,7 +935,7 @@ int run_impl(lbm_handle *h, int64_t max_steps, double tol, int32_t k,
         }
     } guard{h};
     const char *no_defer = std::getenv("LBM_DEFER");  // "0": a finalize launch per interval
-    const bool defer = h->use_tb && h->n_tiles > 0 && h->n_tiles <= kDeferMaxPartials &&
+    const bool defer = h->use_tb && !h->march && h->n_tiles > 0 && h->n_tiles <= kDeferMaxPartials &&
                        !(no_defer && no_defer[0] == '0');
     double *const part = h->partials.as<double>();
     auto half = [&](int j) { return defer ? part + (size_t)(j % 2) * h->n_tiles * 4 : part; };
@@ -888,8 +970,8 @@ int run_impl(lbm_handle *h, int64_t max_steps, double tol, int32_t k,
             const bool by_first = defer && planned > 0 &&
                                   chunk[planned] > steps_per_launch(h->precision, h->tb_variant);
             if (defer && planned > 0 && !by_first)
-                HIP_TRY(launch_finalize_check(half(planned - 1), nparts, ctl, planned - 1, tol,
-                                              h->stream));
+                HIP_TRY(launch_finalize_check(half(planned - 1), h->n_tiles, ctl, planned - 1,
+                                              tol, h->stream));
             h->run_j = planned;
             h->run_part = half(planned);
             h->run_prev = by_first ? half(planned - 1) : nullptr;
@@ -904,7 +986,7 @@ int run_impl(lbm_handle *h, int64_t max_steps, double tol, int32_t k,
             kernels[planned] = h->prof_kernels - k0;
             h->prof_kernels = k0;
             if (!defer)
-                HIP_TRY(launch_finalize_check(half(planned), nparts, ctl, planned, tol,
+                HIP_TRY(launch_finalize_check(half(planned), h->check_parts, ctl, planned, tol,
                                               h->stream));
             cur_after[planned] = h->cur;
         }
@@ -912,7 +994,7 @@ int run_impl(lbm_handle *h, int64_t max_steps, double tol, int32_t k,
         h->run_prev = nullptr;
         h->run_stop_rest = nullptr;
         if (defer)
-            HIP_TRY(launch_finalize_check(half(planned - 1), nparts, ctl, planned - 1, tol,
+            HIP_TRY(launch_finalize_check(half(planned - 1), h->n_tiles, ctl, planned - 1, tol,
                                           h->stream));
         const RunControl *rc = reinterpret_cast<const RunControl *>(h->pinned);
         HIP_TRY(hipMemcpyAsync(h->pinned, ctl, sizeof(RunControl), hipMemcpyDeviceToHost,
@@ -1361,6 +1443,8 @@ int lbm_create_geometry(const lbm_geometry_desc *d, const uint8_t *cell_types,
         h->use_graphs = !(g && g[0] == '0');
         const char *tb = std::getenv("LBM_TB");
         h->use_tb = !(tb && tb[0] == '0');
+        const char *march = std::getenv("LBM_MARCH");
+        if (march && march[0] >= '0' && march[0] <= '9') h->march_env = std::atoi(march);
         HIP_TRY(hipGetDevice(&h->device));
         HIP_TRY(hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device));
         int lds = 0;
@@ -1416,6 +1500,7 @@ int lbm_create_geometry(const lbm_geometry_desc *d, const uint8_t *cell_types,
         HIP_TRY(launch_build_cells(h->types.as<uint8_t>(), h->cell.as<uint16_t>(), h->nx,
                                    h->ny, h->pitch, h->flags, h->stream));
         rebuild_tiles(h);
+        h->march = default_march(h);
         HIP_TRY(hipStreamSynchronize(h->stream));
     } catch (const std::bad_alloc &) {
         delete h;
@@ -2132,6 +2217,7 @@ int lbm_set_tb_variant(lbm_handle *h, int32_t variant) {
     try {
         HIP_TRY(hipSetDevice(h->device));
         h->tb_variant = variant;
+        h->march = 0;
         h->tuned_variant = -1;
         h->tune_ms.clear();  // an explicit choice is kept through exchange steps
         rebuild_tiles(h);
@@ -2156,6 +2242,7 @@ int lbm_autotune(lbm_handle *h, int32_t trial_steps, int32_t *best, double *ms,
         int bv = h->tb_variant;
         double bms = INFINITY;
         std::vector<double> times(nv);
+        h->march = 0;
         for (int v = 0; v < nv; ++v) {
             h->tb_variant = v;
             rebuild_tiles(h);
@@ -2170,6 +2257,18 @@ int lbm_autotune(lbm_handle *h, int32_t trial_steps, int32_t *best, double *ms,
                 bv = v;
             }
         }
+        // the marching sweep, where it is considered, takes the place of the
+        // best shape when it is faster
+        int march = 0;
+        if (may_march(h) && (int64_t)h->N() >= kMarchTuneCells) {
+            h->march = march_steps(h);
+            const double t = with_storage(h->precision, [&](auto x) {
+                return time_handle_steps<decltype(x)>(h, trial_steps);
+            });
+            restore_state(h, sv);
+            if (t < bms) march = h->march;
+        }
+        h->march = march;
         h->tb_variant = bv;
         h->tuned_variant = bv;
         rebuild_tiles(h);

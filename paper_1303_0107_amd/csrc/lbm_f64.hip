@@ -17,6 +17,7 @@
 
 #pragma clang fp contract(off)
 
+#include "lbm_march.h"
 #include "lbm_sweep.h"
 
 namespace lbm {
@@ -117,31 +118,46 @@ struct Cell {
         ux = mx / r;
         uy = my / r;
     }
-    // (bx, by): the inlet velocity (inlet cells) or the velocity a Neumann
-    // outlet imposes (that of its x-1 neighbour's stored state).
+    // Zou-He closures: the three unknown populations, 1, 5, 8 of an inlet
+    // cell (velocity bx) and 3, 7, 6 of an outlet cell (fixed density, or the
+    // velocity (bx, by) of its x-1 neighbour's stored state).
+    __device__ static __forceinline__ void inlet(const double (&f)[9], double bx, double &k1,
+                                                 double &k5, double &k8) {
+        const double rho = (f[0] + f[2] + f[4] + 2.0 * (f[3] + f[6] + f[7])) / (1.0 - bx);
+        const double ru = rho * bx;
+        k1 = f[3] + (2.0 / 3.0) * ru;
+        k5 = f[7] - 0.5 * (f[2] - f[4]) + (1.0 / 6.0) * ru;
+        k8 = f[6] + 0.5 * (f[2] - f[4]) + (1.0 / 6.0) * ru;
+    }
+    __device__ static __forceinline__ void outlet(const double (&f)[9], const SweepArgs<double> &a,
+                                                  double &k3, double &k7, double &k6) {
+        const double uo = -1.0 + (f[0] + f[2] + f[4] + 2.0 * (f[1] + f[5] + f[8])) / a.rho_out;
+        const double ru = a.rho_out * uo;
+        k3 = f[1] - (2.0 / 3.0) * ru;
+        k7 = f[5] + 0.5 * (f[2] - f[4]) - (1.0 / 6.0) * ru;
+        k6 = f[8] - 0.5 * (f[2] - f[4]) - (1.0 / 6.0) * ru;
+    }
+    __device__ static __forceinline__ void neumann(const double (&f)[9], double bx, double by,
+                                                   double &k3, double &k7, double &k6) {
+        const double rho = (f[0] + f[2] + f[4] + 2.0 * (f[1] + f[5] + f[8])) / (1.0 + bx);
+        const double ru = rho * bx, rv = rho * by;
+        k3 = f[1] - (2.0 / 3.0) * ru;
+        k7 = f[5] + 0.5 * (f[2] - f[4]) - (1.0 / 6.0) * ru - 0.5 * rv;
+        k6 = f[8] - 0.5 * (f[2] - f[4]) - (1.0 / 6.0) * ru + 0.5 * rv;
+    }
     __device__ static __forceinline__ void update(double (&f)[9], uint32_t type, double bx,
                                                   double by, const SweepArgs<double> &a,
                                                   double &mass, double &ux, double &uy) {
-        if (type == kInlet) {
-            const double rho = (f[0] + f[2] + f[4] + 2.0 * (f[3] + f[6] + f[7])) / (1.0 - bx);
-            const double ru = rho * bx;
-            f[1] = f[3] + (2.0 / 3.0) * ru;
-            f[5] = f[7] - 0.5 * (f[2] - f[4]) + (1.0 / 6.0) * ru;
-            f[8] = f[6] + 0.5 * (f[2] - f[4]) + (1.0 / 6.0) * ru;
-        } else if (type == kOutlet) {
-            const double uo =
-                -1.0 + (f[0] + f[2] + f[4] + 2.0 * (f[1] + f[5] + f[8])) / a.rho_out;
-            const double ru = a.rho_out * uo;
-            f[3] = f[1] - (2.0 / 3.0) * ru;
-            f[7] = f[5] + 0.5 * (f[2] - f[4]) - (1.0 / 6.0) * ru;
-            f[6] = f[8] - 0.5 * (f[2] - f[4]) - (1.0 / 6.0) * ru;
-        } else if (type == kOutletNeumann) {
-            const double rho = (f[0] + f[2] + f[4] + 2.0 * (f[1] + f[5] + f[8])) / (1.0 + bx);
-            const double ru = rho * bx, rv = rho * by;
-            f[3] = f[1] - (2.0 / 3.0) * ru;
-            f[7] = f[5] + 0.5 * (f[2] - f[4]) - (1.0 / 6.0) * ru - 0.5 * rv;
-            f[6] = f[8] - 0.5 * (f[2] - f[4]) - (1.0 / 6.0) * ru + 0.5 * rv;
-        }
+        if (type == kInlet)
+            inlet(f, bx, f[1], f[5], f[8]);
+        else if (type == kOutlet)
+            outlet(f, a, f[3], f[7], f[6]);
+        else if (type == kOutletNeumann)
+            neumann(f, bx, by, f[3], f[7], f[6]);
+        relax(f, a, mass, ux, uy);
+    }
+    __device__ static __forceinline__ void relax(double (&f)[9], const SweepArgs<double> &a,
+                                                 double &mass, double &ux, double &uy) {
         // Moments and relaxation in the definition's order, without the
         // operations that cannot change a result: terms with a zero velocity
         // component are left out, opposite populations share 3 c.u and
@@ -318,6 +334,12 @@ hipError_t launch_step_batch<double>(const SweepArgs<double> *args, const int32_
                                      const int32_t *blocks, int n_items, bool bc,
                                      hipStream_t s) {
     return sweep::launch_step_batch<f64::Cell>(args, lat, blocks, n_items, bc, s);
+}
+
+template <>
+hipError_t launch_march<double>(const SweepArgs<double> &a, const MarchPlan &p, bool check,
+                                hipStream_t s) {
+    return sweep::launch_march<f64::Cell>(a, p, check, s);
 }
 
 template <>

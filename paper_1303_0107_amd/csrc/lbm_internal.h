@@ -229,6 +229,23 @@ hipError_t launch_tb_batch(const SweepArgs<T> *args, const int32_t *lat, const i
 template <typename T>
 hipError_t launch_step_batch(const SweepArgs<T> *args, const int32_t *lat,
                              const int32_t *blocks, int n_items, bool bc, hipStream_t s);
+// The marching sweep (lbm_march.h): `steps` (1, 2, 4; in float also 6, 7) time steps a launch, one wave per
+// strip of 64 - 2 steps columns and segment of rows.  Interior strips are cut
+// into `segs` segments of `rows` rows, the two edge strips into `edge_segs`
+// of `edge_rows`; `blocks` workgroups of kMarchThreads hold the waves.
+// Lattices of at least two strips without boundary-variant flags.
+constexpr int kMarchThreads = 256;
+struct MarchPlan {
+    int steps, strips, segs, rows, edge_segs, edge_rows, waves, blocks;
+};
+// Waves per SIMD a marching kernel is compiled for: what its registers (12 a
+// step and about 70, twice as many in double) leave of 512.
+constexpr int march_waves(int steps, size_t arith_bytes, bool check) {
+    const int regs = (12 * steps + 70) * (int)(arith_bytes / 4) + (check ? 24 : 0);
+    return regs <= 128 ? 4 : regs <= 168 ? 3 : regs <= 256 ? 2 : 1;
+}
+template <typename T>
+hipError_t launch_march(const SweepArgs<T> &a, const MarchPlan &p, bool check, hipStream_t s);
 int64_t sweep_blocks(int nx, int ny);
 // Limits of lbm_outlet_stats_noalloc (its device scratch is a fixed array).
 constexpr size_t kNoAllocScratchBytes = (size_t)1 << 20;
@@ -344,6 +361,9 @@ hipError_t launch_step_batch<double>(const SweepArgs<double> *args, const int32_
                                      const int32_t *blocks, int n_items, bool bc,
                                      hipStream_t s);
 template <>
+hipError_t launch_march<double>(const SweepArgs<double> &a, const MarchPlan &p, bool check,
+                                hipStream_t s);
+template <>
 hipError_t launch_macro<double>(const MacroArgs<double> &a, hipStream_t s);
 template <>
 hipError_t launch_keys<double>(const KeysArgs &a, hipStream_t s);
@@ -383,6 +403,9 @@ hipError_t launch_import_plane<double>(double *f, const uint16_t *cell, const do
     hipError_t launch_step_batch<T>(const SweepArgs<T> *args, const int32_t *lat,          \
                                     const int32_t *blocks, int n_items, bool bc,           \
                                     hipStream_t s);                                        \
+    template <>                                                                            \
+    hipError_t launch_march<T>(const SweepArgs<T> &a, const MarchPlan &p, bool check,      \
+                               hipStream_t s);                                             \
     template <>                                                                            \
     hipError_t launch_rest_cells<T>(T * f, size_t plane, const int32_t *cells, int count,  \
                                     int nx, int pitch, hipStream_t s);                     \

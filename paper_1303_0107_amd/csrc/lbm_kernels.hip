@@ -27,6 +27,7 @@
 #include "lbm_boundary.h"
 #include "lbm_internal.h"
 #include "lbm_keys.h"
+#include "lbm_march.h"
 #include "lbm_sweep.h"
 
 namespace lbm {
@@ -144,40 +145,63 @@ struct OffsetCell {
         ux = jx * ir;
         uy = jy * ir;
     }
-    // (bx, by): the inlet velocity (inlet cells) or the velocity a Neumann
-    // outlet imposes (that of its x-1 neighbour's stored state).
     __device__ static __forceinline__ void update(CT (&d)[9], uint32_t type, CT bx, CT by,
                                                   const SweepArgs<T> &a, double &mass,
                                                   double &ux_out, double &uy_out) {
+        closure(d, type, bx, by, a);
+        relax(d, a, mass, ux_out, uy_out);
+    }
+    // Zou-He closures: the three unknown populations, 1, 5, 8 of an inlet
+    // cell (velocity bx) and 3, 7, 6 of an outlet cell (fixed density, or the
+    // velocity (bx, by) of its x-1 neighbour's stored state).
+    __device__ static __forceinline__ void inlet(const CT (&d)[9], CT bx, CT &k1, CT &k5, CT &k8) {
 #pragma clang fp contract(on)
+        const CT s = (d[0] + (d[2] + d[4])) + CT(2) * (d[3] + (d[6] + d[7]));
+        const CT dr = (s + bx) * recip(CT(1) - bx);
+        const CT ru = (CT(1) + dr) * bx;
+        const CT h = CT(0.5) * (d[2] - d[4]);
+        k1 = d[3] + (CT(2) / CT(3)) * ru;
+        k5 = d[7] - h + (CT(1) / CT(6)) * ru;
+        k8 = d[6] + h + (CT(1) / CT(6)) * ru;
+    }
+    __device__ static __forceinline__ void outlet(const CT (&d)[9], const SweepArgs<T> &a, CT &k3,
+                                                  CT &k7, CT &k6) {
+#pragma clang fp contract(on)
+        const CT s = (d[0] + (d[2] + d[4])) + CT(2) * (d[1] + (d[5] + d[8]));
+        const CT uo = (s + (CT)a.one_minus_rho_out) * recip((CT)a.rho_out);
+        const CT ru = (CT)a.rho_out * uo;
+        const CT h = CT(0.5) * (d[2] - d[4]);
+        k3 = d[1] - (CT(2) / CT(3)) * ru;
+        k7 = d[5] + h - (CT(1) / CT(6)) * ru;
+        k6 = d[8] - h - (CT(1) / CT(6)) * ru;
+    }
+    __device__ static __forceinline__ void neumann(const CT (&d)[9], CT bx, CT by, CT &k3, CT &k7,
+                                                   CT &k6) {
+#pragma clang fp contract(on)
+        // rho = (1 + s) / (1 + ux): offsets of the Zou-He velocity closure
+        const CT s = (d[0] + (d[2] + d[4])) + CT(2) * (d[1] + (d[5] + d[8]));
+        const CT dr = (s - bx) * recip(CT(1) + bx);
+        const CT ru = (CT(1) + dr) * bx, rv = (CT(1) + dr) * by;
+        const CT h = CT(0.5) * (d[2] - d[4]);
+        k3 = d[1] - (CT(2) / CT(3)) * ru;
+        k7 = d[5] + h - (CT(1) / CT(6)) * ru - CT(0.5) * rv;
+        k6 = d[8] - h - (CT(1) / CT(6)) * ru + CT(0.5) * rv;
+    }
+    __device__ static __forceinline__ void closure(CT (&d)[9], uint32_t type, CT bx, CT by,
+                                                   const SweepArgs<T> &a) {
         if (type == kFluid) {
             // no closure (the common case, tested first)
         } else if (type == kInlet) {
-            const CT s = (d[0] + (d[2] + d[4])) + CT(2) * (d[3] + (d[6] + d[7]));
-            const CT dr = (s + bx) * recip(CT(1) - bx);
-            const CT ru = (CT(1) + dr) * bx;
-            const CT h = CT(0.5) * (d[2] - d[4]);
-            d[1] = d[3] + (CT(2) / CT(3)) * ru;
-            d[5] = d[7] - h + (CT(1) / CT(6)) * ru;
-            d[8] = d[6] + h + (CT(1) / CT(6)) * ru;
+            inlet(d, bx, d[1], d[5], d[8]);
         } else if (type == kOutlet) {
-            const CT s = (d[0] + (d[2] + d[4])) + CT(2) * (d[1] + (d[5] + d[8]));
-            const CT uo = (s + (CT)a.one_minus_rho_out) * recip((CT)a.rho_out);
-            const CT ru = (CT)a.rho_out * uo;
-            const CT h = CT(0.5) * (d[2] - d[4]);
-            d[3] = d[1] - (CT(2) / CT(3)) * ru;
-            d[7] = d[5] + h - (CT(1) / CT(6)) * ru;
-            d[6] = d[8] - h - (CT(1) / CT(6)) * ru;
+            outlet(d, a, d[3], d[7], d[6]);
         } else if (type == kOutletNeumann) {
-            // rho = (1 + s) / (1 + ux): offsets of the Zou-He velocity closure
-            const CT s = (d[0] + (d[2] + d[4])) + CT(2) * (d[1] + (d[5] + d[8]));
-            const CT dr = (s - bx) * recip(CT(1) + bx);
-            const CT ru = (CT(1) + dr) * bx, rv = (CT(1) + dr) * by;
-            const CT h = CT(0.5) * (d[2] - d[4]);
-            d[3] = d[1] - (CT(2) / CT(3)) * ru;
-            d[7] = d[5] + h - (CT(1) / CT(6)) * ru - CT(0.5) * rv;
-            d[6] = d[8] - h - (CT(1) / CT(6)) * ru + CT(0.5) * rv;
+            neumann(d, bx, by, d[3], d[7], d[6]);
         }
+    }
+    __device__ static __forceinline__ void relax(CT (&d)[9], const SweepArgs<T> &a, double &mass,
+                                                 double &ux_out, double &uy_out) {
+#pragma clang fp contract(on)
         // The relaxation in moment form.  The sums and differences of opposite
         // populations (a: 1 +- 3, b: 2 +- 4) and of the four diagonal ones
         // are, up to factors, nine moments: density, the two momenta, and six
@@ -505,6 +529,11 @@ static inline dim3 grid_cells(int ncols, int ny) {
                                     const int32_t *blocks, int n_items, bool bc,         \
                                     hipStream_t s) {                                     \
         return sweep::launch_step_batch<CELL>(args, lat, blocks, n_items, bc, s);        \
+    }                                                                                    \
+    template <>                                                                          \
+    hipError_t launch_march<T>(const SweepArgs<T> &a, const MarchPlan &p, bool check,    \
+                               hipStream_t s) {                                          \
+        return sweep::launch_march<CELL>(a, p, check, s);                                \
     }
 LBM_OFFSET_LAUNCHERS(float, F32Cell)
 LBM_OFFSET_LAUNCHERS(h16, H16Cell)
