@@ -148,13 +148,17 @@ struct Cell {
     __device__ static __forceinline__ void update(double (&f)[9], uint32_t type, double bx,
                                                   double by, const SweepArgs<double> &a,
                                                   double &mass, double &ux, double &uy) {
+        closure(f, type, bx, by, a);
+        relax(f, a, mass, ux, uy);
+    }
+    __device__ static __forceinline__ void closure(double (&f)[9], uint32_t type, double bx,
+                                                   double by, const SweepArgs<double> &a) {
         if (type == kInlet)
             inlet(f, bx, f[1], f[5], f[8]);
         else if (type == kOutlet)
             outlet(f, a, f[3], f[7], f[6]);
         else if (type == kOutletNeumann)
             neumann(f, bx, by, f[3], f[7], f[6]);
-        relax(f, a, mass, ux, uy);
     }
     __device__ static __forceinline__ void relax(double (&f)[9], const SweepArgs<double> &a,
                                                  double &mass, double &ux, double &uy) {

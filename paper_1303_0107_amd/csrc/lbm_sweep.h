@@ -62,10 +62,12 @@ __device__ __forceinline__ size_t general_src(uint32_t cw, int i, int col, int r
 }
 
 // LDS stores of one region cell in a step: plane i of copy b sits at
-// (2i + b) * PL elements, reached from one of three LDS addresses (planes 0-3,
-// 4-7, 8), so that every store's remaining offset fits the 16-bit immediate
-// of an LDS instruction.  The addresses are made opaque once per launch so
-// that they stay in registers instead of being recomputed at every step.
+// (2i + b) * PL elements.  Planes 1-4 and 5-8 are reached from one LDS address
+// each, so that every store's remaining offset fits the immediates of an LDS
+// instruction and two planes go out in one.  The addresses are made opaque
+// once per launch so that they stay in registers instead of being recomputed
+// at every step.  The rest population of a cell never leaves its thread's
+// registers (plane 0 is read by a Neumann outlet's neighbour only).
 template <typename T, int PL>
 struct StoreBases {
     // the stored bits (the 16-bit formats are classes without an assignment
@@ -74,26 +76,20 @@ struct StoreBases {
         sizeof(T) == 8, uint64_t,
         typename std::conditional<sizeof(T) == 4, uint32_t, uint16_t>::type>::type;
     using LdsBits = __attribute__((address_space(3))) Bits;
-    LdsBits *b[3];
+    LdsBits *b[2];
     __device__ __forceinline__ void set(T *L, int pos) {
         LdsBits *p = (LdsBits *)reinterpret_cast<Bits *>(L + pos);
-        b[0] = p;
-        b[1] = p + 8 * PL;
-        b[2] = p + 16 * PL;
+        b[0] = p + 2 * PL;
+        b[1] = p + 10 * PL;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) asm volatile("" : "+v"(b[k]));
+        for (int k = 0; k < 2; ++k) asm volatile("" : "+v"(b[k]));
     }
-    // Population i into copy C.
+    // Population i >= 1 into copy C.
     template <int C>
     __device__ __forceinline__ void put(int i, T v) const {
         Bits w;
         __builtin_memcpy(&w, &v, sizeof(T));
-        if (i < 4)
-            b[0][(2 * i + C) * PL] = w;
-        else if (i < 8)
-            b[1][(2 * (i - 4) + C) * PL] = w;
-        else
-            b[2][C * PL] = w;
+        b[(i - 1) / 4][(2 * ((i - 1) % 4) + C) * PL] = w;
     }
 };
 
@@ -341,8 +337,23 @@ __global__ __launch_bounds__(256) void step_batch_kernel(
 // compile-time constant; each pull then reads a per-cell LDS byte address,
 // computed once per launch, plus an immediate offset.  A cell's depth (its
 // distance to the region edge; 0 for solid cells) bounds the steps it can
-// take: it is advanced at step s exactly when depth >= s, and is a tile cell
+// take: it is valid at step s exactly when depth >= s, and is a tile cell
 // exactly when depth >= H.
+//
+// A step is bound by the latency of its chain (pulls, update, stores,
+// barrier) and by LDS traffic, no longer by vector issue (an FP32 instruction
+// takes a wave 2.3-2.8 cycles with two or more waves on the SIMD, 4.5-5 with
+// one).  So the rest population stays in a register, 8 of 9 populations going
+// through LDS, and a row is advanced whole, by a scalar branch, while any of
+// its cells has the depth: what the lanes beyond it compute is never read by
+// a valid cell, and solid cells are never read at all, so neither the pulls
+// nor the stores need a lane mask; only the tile's cells are written to HBM.
+// us per launch against lane masks and nine populations in LDS: 1024 x 512
+// distributor, (32,9), 12.2 -> 11.9; 1024 x 512 channel, (16,4), 15.9 -> 15.4
+// and (32,8) 34.2 -> 32.4; 256 x 128 distributor, (32,9), 11.9 -> 10.6.
+// Reading both of a wave's rows before relaxing either was slower (12.1,
+// 33.2), and 67 registers in place of 64 leave the 16-row shapes one
+// workgroup a CU (15.4 -> 20.8).
 template <class Cell, int RH, int H, int NT, bool CHECK, bool BC, bool HALT, bool PREV>
 __device__ __forceinline__ void tb_body(const SweepArgs<typename Cell::T> &a, const int t,
                                         const int steps, double *part_out) {
@@ -356,7 +367,8 @@ __device__ __forceinline__ void tb_body(const SweepArgs<typename Cell::T> &a, co
     T *L = reinterpret_cast<T *>(lds_raw);
 
     const int ox = (t & 0xffff) * IW - H, oy = (t >> 16) * IH - H;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     RunGate<NT, HALT, PREV> gate;
     gate.read(a);  // beside the region's loads
     const int gx = ox + lane;
@@ -364,9 +376,12 @@ __device__ __forceinline__ void tb_body(const SweepArgs<typename Cell::T> &a, co
 
     uint32_t cw[CPT];
     int depth[CPT];
+    int reach[CPT];        // largest depth in the row, at most H (the same in every lane)
+    bool closing[CPT];     // the row has inlet or outlet cells (the same in every lane)
     const T *src[CPT][9];  // LDS address of each pull in copy 0
     StoreBases<T, PL> dst[CPT];
     UinT<T> uin[CPT];      // inlet velocity of the thread's cells, read once per launch
+    CT rest[CPT];          // population 0
     T v[CPT][9];
     size_t n[CPT];
     // The cell words of all the thread's cells are read first, then all their
@@ -397,60 +412,83 @@ __device__ __forceinline__ void tb_body(const SweepArgs<typename Cell::T> &a, co
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
         const int pos = (wave + c * NW) * RW + lane;
+        rest[c] = Cell::load(v[c][0]);
+        if (BC) L[pos] = v[c][0];
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
+        for (int i = 1; i < 9; ++i) {
             L[2 * i * PL + pos] = v[c][i];
-            const bool wall = i > 0 && ((cw[c] >> (i - 1)) & 1u);
+            // a wall's pull, and the unused ones of the region's edge, are the
+            // cell's own
+            const bool wall = ((cw[c] >> (i - 1)) & 1u) || depth[c] == 0;
             const int e = wall ? 2 * kOpp[i] * PL + pos : 2 * i * PL + pos - kCy[i] * RW - kCx[i];
             src[c][i] = L + e;
         }
         dst[c].set(L, pos);
+        reach[c] = 0;
+#pragma unroll
+        for (int k = 1; k <= H; ++k) reach[c] += __any(depth[c] >= k) ? 1 : 0;
+        reach[c] = __builtin_amdgcn_readfirstlane(reach[c]);
+        closing[c] = __any(cell_type(cw[c]) > kFluid);
     }
     if (gate.ended(a)) return;
     __syncthreads();
     if (gate.ends_now(a)) return;
 
     double part[4] = {0.0, 0.0, 0.0, 0.0};
+    // The populations cell c pulls at a step reading copy B, and the boundary
+    // velocity of its closure.
+    auto pull = [&](auto copy, const int c, CT (&f)[9], CT &bx, CT &by) {
+        constexpr int B = decltype(copy)::value;
+        const int ry = wave + c * NW, gy = oy + ry, pos = ry * RW + lane;
+        const uint32_t type = update_type(cw[c]);
+        bx = type == kInlet ? (CT)uin[c] : CT(0);
+        by = CT(0);
+        if (BC && type == kOutletNeumann && (cw[c] & kWordLeftLive)) {
+            CT g[9];
+#pragma unroll
+            for (int i = 0; i < 9; ++i) g[i] = Cell::load(L[(2 * i + B) * PL + pos - 1]);
+            Cell::velocity(g, bx, by);
+        }
+        f[0] = rest[c];
+        if (BC && (cw[c] & kWordGeneral)) {
+#pragma unroll
+            for (int i = 1; i < 9; ++i)
+                f[i] = Cell::load(
+                    L[general_src(cw[c], i, lane, ry, gy, a.ny, a.flags, 2 * PL, RW) + B * PL]);
+        } else {
+#pragma unroll
+            for (int i = 1; i < 9; ++i) f[i] = Cell::load(src[c][i][B * PL]);
+        }
+    };
+    auto advance = [&](auto copy, const int c, const bool last) {
+        constexpr int B = decltype(copy)::value;
+        CT f[9], bx, by;
+        pull(copy, c, f, bx, by);
+        if (closing[c]) Cell::closure(f, update_type(cw[c]), bx, by, a);
+        double mass, ux, uy;
+        Cell::relax(f, a, mass, ux, uy);
+        if (last) {
+            if (depth[c] >= H) {
+                const size_t m = (size_t)(oy + wave + c * NW) * a.pitch + gx;
+#pragma unroll
+                for (int i = 0; i < 9; ++i) a.fout[(size_t)i * a.plane + m] = Cell::store(f[i]);
+                if (CHECK) check_terms(a, m, mass, ux, uy, part);
+            }
+        } else {
+            const T r = Cell::store(f[0]);
+            rest[c] = Cell::load(r);
+            if (BC) L[(1 - B) * PL + (wave + c * NW) * RW + lane] = r;
+#pragma unroll
+            for (int i = 1; i < 9; ++i) dst[c].template put<1 - B>(i, Cell::store(f[i]));
+        }
+    };
     // One step reading copy B and writing copy 1 - B; true when it was the last.
     auto step = [&](auto copy, const int s) -> bool {
-        constexpr int B = decltype(copy)::value;
         const bool last = s == steps;
         const int need = last ? H : s;
 #pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-            if (depth[c] < need) continue;
-            const int ry = wave + c * NW, gy = oy + ry, pos = ry * RW + lane;
-            const uint32_t type = update_type(cw[c]);
-            CT bx = type == kInlet ? (CT)uin[c] : CT(0), by = CT(0);
-            if (BC && type == kOutletNeumann && (cw[c] & kWordLeftLive)) {
-                CT g[9];
-#pragma unroll
-                for (int i = 0; i < 9; ++i) g[i] = Cell::load(L[(2 * i + B) * PL + pos - 1]);
-                Cell::velocity(g, bx, by);
-            }
-            CT f[9];
-            if (BC && (cw[c] & kWordGeneral)) {
-#pragma unroll
-                for (int i = 0; i < 9; ++i)
-                    f[i] = Cell::load(
-                        L[general_src(cw[c], i, lane, ry, gy, a.ny, a.flags, 2 * PL, RW) + B * PL]);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 9; ++i)
-                    f[i] = Cell::load(src[c][i][B * PL]);
-            }
-            double mass, ux, uy;
-            Cell::update(f, type, bx, by, a, mass, ux, uy);
-            if (last) {
-                const size_t n = (size_t)gy * a.pitch + gx;
-#pragma unroll
-                for (int i = 0; i < 9; ++i) a.fout[(size_t)i * a.plane + n] = Cell::store(f[i]);
-                if (CHECK) check_terms(a, n, mass, ux, uy, part);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 9; ++i) dst[c].template put<1 - B>(i, Cell::store(f[i]));
-            }
-        }
+        for (int c = 0; c < CPT; ++c)
+            if (reach[c] >= need) advance(copy, c, last);
         if (last) return true;
         __syncthreads();
         return false;
@@ -722,6 +760,7 @@ __device__ __forceinline__ void tb_body_compact(const SweepArgs<typename Cell::T
     const T *src[CPT][9];  // LDS address of each pull of the thread's entries in copy 0
     StoreBases<T, PL> dst[CPT];
     UinT<T> uin[CPT];      // inlet velocity of the thread's entries, read once per launch
+    CT rest[CPT];          // population 0 of the thread's entries
 #pragma unroll
     for (int m = 0; m < CPT; ++m) {
         const int j = threadIdx.x + m * NT;
@@ -729,10 +768,11 @@ __device__ __forceinline__ void tb_body_compact(const SweepArgs<typename Cell::T
         const uint32_t c = ent[m] >> 16;
         const int pos = (int)(ent[m] & 0xffffu);
         dst[m].set(L, pos);
+        rest[m] = Cell::load(L[pos]);
         uin[m] = (j < n_all && cell_type(c) == kInlet) ? a.uin[oy + pos / RW] : UinT<T>(0);
 #pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            const bool wall = i > 0 && ((c >> (i - 1)) & 1u);
+        for (int i = 1; i < 9; ++i) {
+            const bool wall = (c >> (i - 1)) & 1u;
             const int e = wall ? 2 * kOpp[i] * PL + pos : 2 * i * PL + pos - kCy[i] * RW - kCx[i];
             src[m][i] = L + e;
         }
@@ -761,14 +801,15 @@ __device__ __forceinline__ void tb_body_compact(const SweepArgs<typename Cell::T
                 Cell::velocity(g, bx, by);
             }
             CT f[9];
+            f[0] = rest[m];
             if (BC && (c & kWordGeneral)) {
 #pragma unroll
-                for (int i = 0; i < 9; ++i)
+                for (int i = 1; i < 9; ++i)
                     f[i] = Cell::load(
                         L[general_src(c, i, lx, ry, gy, a.ny, a.flags, 2 * PL, RW) + B * PL]);
             } else {
 #pragma unroll
-                for (int i = 0; i < 9; ++i) f[i] = Cell::load(src[m][i][B * PL]);
+                for (int i = 1; i < 9; ++i) f[i] = Cell::load(src[m][i][B * PL]);
             }
             double mass, ux, uy;
             Cell::update(f, type, bx, by, a, mass, ux, uy);
@@ -778,8 +819,11 @@ __device__ __forceinline__ void tb_body_compact(const SweepArgs<typename Cell::T
                 for (int i = 0; i < 9; ++i) a.fout[(size_t)i * a.plane + n] = Cell::store(f[i]);
                 if (CHECK) check_terms(a, n, mass, ux, uy, part);
             } else {
+                const T r = Cell::store(f[0]);
+                rest[m] = Cell::load(r);
+                if (BC) L[(1 - B) * PL + pos] = r;
 #pragma unroll
-                for (int i = 0; i < 9; ++i) dst[m].template put<1 - B>(i, Cell::store(f[i]));
+                for (int i = 1; i < 9; ++i) dst[m].template put<1 - B>(i, Cell::store(f[i]));
             }
         }
         if (last) return true;
