@@ -1056,10 +1056,8 @@ int run_impl(lbm_handle *h, int64_t max_steps, double tol, int32_t k,
     return status;
 }
 
-// Boundary sums of the current state and of the state one step later (a
-// single sweep into the other population buffer, which holds nothing of use
-// between steps; the current state and buffer parity are untouched), then
-// the mass of the current state.  bout: 2 * (2 n_out + 5) sums, the current
+// Boundary sums of the current state and of the state one step later, then
+// the mass of the current state (no population buffer is written).  bout: 2 * (2 n_out + 5) sums, the current
 // state's first.
 template <typename T>
 void stats_impl(lbm_handle *h, std::vector<double> &bout, double &mass) {
@@ -1071,11 +1069,7 @@ void stats_impl(lbm_handle *h, std::vector<double> &bout, double &mass) {
     double *bo = h->bnd.as<double>();
     const int32_t *y0 = h->out_rows.as<int32_t>();
     const int32_t *y1 = y0 + std::max(n_out, 1);
-    HIP_TRY(launch_boundary<T>(a, y0, y1, n_out, bo, h->stream));
-    HIP_TRY(launch_sweep<T>(sweep_args<T>(h, false), false, h->stream));
-    MacroArgs<T> next = a;
-    next.f = h->f[1 - h->cur].as<T>();
-    HIP_TRY(launch_boundary<T>(next, y0, y1, n_out, bo + nb, h->stream));
+    HIP_TRY(launch_boundary<T>(sweep_args<T>(h, false), y0, y1, n_out, bo, h->stream));
     HIP_TRY(launch_mass<T>(a, h->partials.as<double>(), h->stream));
     HIP_TRY(launch_finalize1(h->partials.as<double>(), sweep_blocks(h->nx, h->ny),
                              bo + 2 * nb, h->stream));
@@ -1723,11 +1717,7 @@ void stats_noalloc_impl(lbm_handle *h, double *scr, double *host) {
     const int32_t *y0 = h->out_rows.as<int32_t>();
     const int32_t *y1 = y0 + std::max(n_out, 1);
     double *partials = scr + 2 * nb + 1;
-    HIP_TRY(launch_boundary<T>(a, y0, y1, n_out, scr, h->stream));
-    HIP_TRY(launch_sweep<T>(sweep_args<T>(h, false), false, h->stream));
-    MacroArgs<T> next = a;
-    next.f = h->f[1 - h->cur].as<T>();
-    HIP_TRY(launch_boundary<T>(next, y0, y1, n_out, scr + nb, h->stream));
+    HIP_TRY(launch_boundary<T>(sweep_args<T>(h, false), y0, y1, n_out, scr, h->stream));
     HIP_TRY(launch_mass<T>(a, partials, h->stream));
     HIP_TRY(launch_finalize1(partials, sweep_blocks(h->nx, h->ny), scr + 2 * nb, h->stream));
     HIP_TRY(hipMemcpyAsync(host, scr, (2 * nb + 1) * sizeof(double), hipMemcpyDeviceToHost,

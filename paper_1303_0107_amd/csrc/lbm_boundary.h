@@ -1,14 +1,23 @@
-// The inlet-and-outlets task of the boundary sums (Sec. 2.3 step 5, Eqs.
-// 9-11; the pressure drop of Eq. 4), shared by the storage forms.
+// The boundary sums of the outlet statistics (Sec. 2.3 step 5, Eqs. 9-11; the
+// pressure drop of Eq. 4), shared by the storage forms.
 //
-// One workgroup of kBoundaryThreads threads sums, each as a running sum in
-// increasing y (the order of a sequential loop over the rows): the density
-// over every outlet cell of column nx - 1, and the x momentum and the
-// density over the inlet cells of column 0, with the two cell counts.  The
-// threads first take up to kBoundarySpan rows (kBoundaryRowsPerThread each)
-// and leave each row's values in LDS; thread 0 then adds them up in row
-// order, with selects instead of branches so that the additions follow each
-// other closely.
+// One launch sums over the stored state and over the state one time step
+// later.  Only the boundary columns of the later state are needed, so their
+// cells take the step here, from the stored state, and nothing is written
+// back.  Workgroup (k, s) of the grid (n_out + 1, 2): outlet k (k < n_out) or
+// the ends (k == n_out: the inlet cells and all outlet cells) of state s.
+//
+// Every sum is a running sum in increasing y, the order of a sequential loop
+// over the rows.  What bounds it is that chain of double additions, so the
+// rows' values are first read by all lanes at once, and then one wave adds
+// 64 of them at a time, taking lane after lane as a scalar operand: three
+// instructions a row, none of them waiting for memory.  Rows without a
+// boundary cell add 0.0, which leaves the sum as it is, and 64 rows without
+// any are passed over.  The three sums of the ends run in three waves.
+// Before, each state had a launch of its own (18-160 us), with the rows'
+// values taken from LDS one by one in a single thread and a whole time step in
+// between: advancing and judging 48 candidates takes 19.7 ms in place of 21.1,
+// 29 us less a call.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -21,64 +30,95 @@ namespace lbm {
 constexpr int kBoundaryThreads = 256, kBoundaryRowsPerThread = 4,
               kBoundarySpan = kBoundaryThreads * kBoundaryRowsPerThread;
 
-// at(n, rho, jx): density and x momentum of the cell at pitched index n.
-// o: [flow_in, rho_in, count_in, count_out, rho_out] (valid in thread 0).
+// sum + v of lane 0 + v of lane 1 + ... + v of lane m - 1, one after another.
+__device__ __forceinline__ double add_lanes(double sum, double v, int m) {
+    const uint64_t w = (uint64_t)__double_as_longlong(v);
+    const int lo = (int)(uint32_t)w, hi = (int)(uint32_t)(w >> 32);
+    auto lane = [&](int t) {
+        const uint64_t b = (uint64_t)(uint32_t)__builtin_amdgcn_readlane(lo, t) |
+                           ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, t) << 32);
+        return __longlong_as_double((long long)b);
+    };
+    if (m == 64) {
+#pragma unroll 16
+        for (int t = 0; t < 64; ++t) sum += lane(t);
+    } else {
+        for (int t = 0; t < m; ++t) sum += lane(t);
+    }
+    return sum;
+}
+
+// at(x, y, rho, jx): density and x momentum of the boundary cell (x, y).
+// out: [flow_0 .. flow_{n-1}, rho_0 .. rho_{n-1}, flow_in, rho_in, count_in,
+//       count_out, rho_out]
 template <class At>
-__device__ __forceinline__ void boundary_ends(const uint16_t *cell, int nx, int ny, int pitch,
-                                              At at, double (&o)[5]) {
-    __shared__ double s_ro[kBoundarySpan], s_ri[kBoundarySpan], s_ji[kBoundarySpan];
-    __shared__ uint8_t s_kind[kBoundarySpan];  // bit 0: outlet cell, bit 1: inlet cell
-    const int t = threadIdx.x;
-    double fl = 0.0, rin = 0.0, cin = 0.0, cout = 0.0, rout = 0.0;
+__device__ __forceinline__ void boundary_sums(const uint16_t *cell, int nx, int ny, int pitch,
+                                              const int32_t *out_y0, const int32_t *out_y1,
+                                              int n_out, double *out, At at) {
+    const int k = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    if (k < n_out) {
+        if (t >= 64) return;  // one wave per outlet
+        const int y0 = out_y0[k], y1 = out_y1[k];
+        double fl = 0.0, rs = 0.0;
+        for (int c = y0; c <= y1; c += 64) {
+            double r = 0.0, j = 0.0;
+            if (c + lane <= y1) at(nx - 1, c + lane, r, j);
+            const int m = min(64, y1 - c + 1);
+            fl = add_lanes(fl, j, m);
+            rs = add_lanes(rs, r, m);
+        }
+        if (lane == 0) {
+            out[k] = fl;
+            out[n_out + k] = rs;
+        }
+        return;
+    }
+    __shared__ double s_v[3][kBoundarySpan];  // outlet rho, inlet rho, inlet jx of each row
+    double sum = 0.0;
+    int64_t count = 0;
     for (int c0 = 0; c0 < ny; c0 += kBoundarySpan) {
-        // The cell words of all of a thread's rows first, then the
-        // populations of all of them at once: rows that hold no boundary
-        // cell (and rows past the end) read cell 0 instead, which every lane
-        // shares, so that no branch separates the loads and no other cache
-        // line is touched; their values are dropped by the selects.
-        bool out[kBoundaryRowsPerThread], in[kBoundaryRowsPerThread];
+        // The cell words of all of a thread's rows first, then their
+        // populations.  Rows that hold no boundary cell are not read.
+        bool is_out[kBoundaryRowsPerThread], is_in[kBoundaryRowsPerThread];
 #pragma unroll
         for (int q = 0; q < kBoundaryRowsPerThread; ++q) {
             const int y = c0 + q * kBoundaryThreads + t;
             const size_t n0 = (size_t)min(y, ny - 1) * pitch;
-            const uint32_t wo = cell[n0 + nx - 1], wi = cell[n0];
-            out[q] = (y < ny) & (cell_type(wo) == kOutlet);
-            in[q] = (y < ny) & (cell_type(wi) == kInlet);
+            is_out[q] = (y < ny) & (cell_type(cell[n0 + nx - 1]) == kOutlet);
+            is_in[q] = (y < ny) & (cell_type(cell[n0]) == kInlet);
         }
 #pragma unroll
         for (int q = 0; q < kBoundaryRowsPerThread; ++q) {
             const int r = q * kBoundaryThreads + t;
-            const size_t n0 = (size_t)(c0 + r) * pitch;
-            double ro, jo, ri, ji;
-            at(out[q] ? n0 + nx - 1 : 0, ro, jo);
-            at(in[q] ? n0 : 0, ri, ji);
-            s_ro[r] = out[q] ? ro : 0.0;
-            s_ri[r] = in[q] ? ri : 0.0;
-            s_ji[r] = in[q] ? ji : 0.0;
-            s_kind[r] = (uint8_t)((out[q] ? 1 : 0) | (in[q] ? 2 : 0));
+            double ro = 0.0, jo, ri = 0.0, ji = 0.0;
+            if (is_out[q]) at(nx - 1, c0 + r, ro, jo);
+            if (is_in[q]) at(0, c0 + r, ri, ji);
+            s_v[0][r] = ro;
+            s_v[1][r] = ri;
+            s_v[2][r] = ji;
         }
         __syncthreads();
-        if (t == 0) {
+        if (wave < 3) {
             const int m = min(kBoundarySpan, ny - c0);
-#pragma unroll 8
-            for (int r = 0; r < m; ++r) {
-                const int kd = s_kind[r];
-                const bool out = (kd & 1) != 0, in = (kd & 2) != 0;
-                const double a = rout + s_ro[r], b = fl + s_ji[r], c = rin + s_ri[r];
-                rout = out ? a : rout;
-                cout = out ? cout + 1.0 : cout;
-                fl = in ? b : fl;
-                rin = in ? c : rin;
-                cin = in ? cin + 1.0 : cin;
+            for (int r = 0; r < m; r += 64) {
+                const int y = c0 + r + lane;
+                const size_t n0 = (size_t)min(y, ny - 1) * pitch;
+                const bool has = (y < ny) & (wave == 0 ? cell_type(cell[n0 + nx - 1]) == kOutlet
+                                                       : cell_type(cell[n0]) == kInlet);
+                const uint64_t any = __ballot(has);
+                if (any == 0) continue;
+                count += __popcll(any);
+                sum = add_lanes(sum, has ? s_v[wave][r + lane] : 0.0, 64);
             }
         }
         __syncthreads();
     }
-    o[0] = fl;
-    o[1] = rin;
-    o[2] = cin;
-    o[3] = cout;
-    o[4] = rout;
+    if (lane == 0 && wave < 3) {
+        double *o = out + 2 * n_out;  // flow_in, rho_in, count_in, count_out, rho_out
+        o[wave == 0 ? 4 : wave == 1 ? 1 : 0] = sum;
+        if (wave == 0) o[3] = (double)count;
+        if (wave == 1) o[2] = (double)count;
+    }
 }
 
 }  // namespace lbm

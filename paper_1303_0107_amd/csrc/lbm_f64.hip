@@ -229,46 +229,30 @@ __global__ __launch_bounds__(256) void mass_kernel(MacroArgs<double> a,
     if (tid == 0) partials[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = v[0];
 }
 
-// Boundary sums in increasing y: workgroup k < n_out sums the x momentum of
-// outlet k; workgroup n_out sums x momentum and density over the inlet cells
-// and density over all outlet cells (one running sum each).  out layout:
-// [flow_0..flow_{n-1}, unused n, flow_in, rho_in, count_in, count_out, rho_out]
-__global__ __launch_bounds__(kBoundaryThreads) void boundary_kernel(MacroArgs<double> a,
+// Boundary sums (lbm_boundary.h) of the stored state (a.fin) and of the state
+// one step later; out: the stored state's 2 n_out + 5 sums, then the later's.
+template <bool BC>
+__global__ __launch_bounds__(kBoundaryThreads) void boundary_kernel(SweepArgs<double> a,
                                                                     const int32_t *out_y0,
                                                                     const int32_t *out_y1,
                                                                     int n_out, double *out) {
-    // The sums take the rows in increasing y one at a time (the oracle's
-    // sequential order): an outlet's rows are read by one wave, 64 at once,
-    // the inlet and all outlet cells by the whole workgroup (boundary_ends).
-    const int k = blockIdx.x, lane = threadIdx.x;
-    auto at = [&](size_t n, double &r, double &mx) {
-        double f[9], my;
+    if (blockIdx.y == 0)
+        boundary_sums(a.cell, a.nx, a.ny, a.pitch, out_y0, out_y1, n_out, out,
+                      [&](int x, int y, double &r, double &mx) {
+                          const size_t n = (size_t)y * a.pitch + x;
+                          double f[9], my;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) f[i] = a.f[(size_t)i * a.plane + n];
-        moments(f, r, mx, my);
-    };
-    if (k < n_out) {
-        if (threadIdx.x >= 64) return;  // one wave per outlet
-        const int y0 = out_y0[k], y1 = out_y1[k];
-        double fl = 0.0;
-        for (int c = y0; c <= y1; c += 64) {
-            double r = 0.0, mx = 0.0;
-            if (c + lane <= y1) at((size_t)(c + lane) * a.pitch + (a.nx - 1), r, mx);
-            const int m = min(64, y1 - c + 1);
-            for (int t = 0; t < m; ++t) fl += __shfl(mx, t, 64);
-        }
-        if (lane == 0) {
-            out[k] = fl;
-            out[n_out + k] = 0.0;
-        }
-    } else {
-        double o[5];
-        boundary_ends(a.cell, a.nx, a.ny, a.pitch,
-                      [&](size_t n, double &r, double &mx) { at(n, r, mx); }, o);
-        if (lane == 0)
-#pragma unroll
-            for (int q = 0; q < 5; ++q) out[2 * n_out + q] = o[q];
-    }
+                          for (int i = 0; i < 9; ++i) f[i] = a.fin[(size_t)i * a.plane + n];
+                          moments(f, r, mx, my);
+                      });
+    else
+        boundary_sums(a.cell, a.nx, a.ny, a.pitch, out_y0, out_y1, n_out, out + 2 * n_out + 5,
+                      [&](int x, int y, double &r, double &mx) {
+                          double f[9], m, ux, uy, my;
+                          sweep::step_cell<Cell, BC>(a, x, y, a.cell[(size_t)y * a.pitch + x], f,
+                                                     m, ux, uy);
+                          moments(f, r, mx, my);
+                      });
 }
 
 __global__ void rest_cells_kernel(double *f, size_t plane, const int32_t *cells,
@@ -371,11 +355,13 @@ hipError_t launch_mass<double>(const MacroArgs<double> &a, double *partials,
 }
 
 template <>
-hipError_t launch_boundary<double>(const MacroArgs<double> &a, const int32_t *y0,
-                                   const int32_t *y1, int n_out, double *out,
-                                   hipStream_t s) {
-    hipLaunchKernelGGL(f64::boundary_kernel, dim3((unsigned)(n_out + 1)), dim3(kBoundaryThreads),
-                       0, s, a, y0, y1, n_out, out);
+hipError_t launch_boundary<double>(const SweepArgs<double> &a, const int32_t *y0,
+                                   const int32_t *y1, int n_out, double *out, hipStream_t s) {
+    const dim3 g((unsigned)(n_out + 1), 2), b(kBoundaryThreads);
+    if (a.flags)
+        hipLaunchKernelGGL(f64::boundary_kernel<true>, g, b, 0, s, a, y0, y1, n_out, out);
+    else
+        hipLaunchKernelGGL(f64::boundary_kernel<false>, g, b, 0, s, a, y0, y1, n_out, out);
     return hipGetLastError();
 }
 

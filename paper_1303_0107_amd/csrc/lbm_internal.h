@@ -281,8 +281,10 @@ template <typename T>
 hipError_t launch_macro(const MacroArgs<T> &a, hipStream_t s);
 template <typename T>
 hipError_t launch_mass(const MacroArgs<T> &a, double *partials, hipStream_t s);
+// Boundary sums of the state a.fin and of the state one step later (a.fout is
+// not touched): 2 (2 n_out + 5) doubles.
 template <typename T>
-hipError_t launch_boundary(const MacroArgs<T> &a, const int32_t *y0,
+hipError_t launch_boundary(const SweepArgs<T> &a, const int32_t *y0,
                            const int32_t *y1, int n_out, double *out,
                            hipStream_t s);
 hipError_t launch_build_cells(const uint8_t *types, uint16_t *cell, int nx,
@@ -372,7 +374,7 @@ hipError_t launch_flip<double>(const FlipArgs &a, hipStream_t s);
 template <>
 hipError_t launch_mass<double>(const MacroArgs<double> &a, double *partials, hipStream_t s);
 template <>
-hipError_t launch_boundary<double>(const MacroArgs<double> &a, const int32_t *y0,
+hipError_t launch_boundary<double>(const SweepArgs<double> &a, const int32_t *y0,
                                    const int32_t *y1, int n_out, double *out, hipStream_t s);
 template <>
 hipError_t launch_rest_cells<double>(double *f, size_t plane, const int32_t *cells,
@@ -406,6 +408,10 @@ hipError_t launch_import_plane<double>(double *f, const uint16_t *cell, const do
     template <>                                                                            \
     hipError_t launch_march<T>(const SweepArgs<T> &a, const MarchPlan &p, bool check,      \
                                hipStream_t s);                                             \
+    template <>                                                                            \
+    hipError_t launch_boundary<T>(const SweepArgs<T> &a, const int32_t *y0,                \
+                                  const int32_t *y1, int n_out, double *out,               \
+                                  hipStream_t s);                                          \
     template <>                                                                            \
     hipError_t launch_rest_cells<T>(T * f, size_t plane, const int32_t *cells, int count,  \
                                     int nx, int pitch, hipStream_t s);                     \

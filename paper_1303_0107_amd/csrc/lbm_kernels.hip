@@ -344,54 +344,41 @@ __global__ __launch_bounds__(256) void mass_kernel(MacroArgs<T> a,
     if (tid == 0) partials[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = v[0];
 }
 
-// Boundary sums (Sec. 4.2) in increasing y: workgroup k < n_out sums rho u_x
-// and rho over outlet k's rows y0..y1 (column nx-1); workgroup n_out sums
-// over the inlet cells of column 0 and the density over all outlet cells.  out:
-// [flow_0..flow_{n-1}, rho_0..rho_{n-1}, flow_in, rho_in, count_in,
-//  count_out, rho_out]
-template <typename T>
-__global__ __launch_bounds__(kBoundaryThreads) void boundary_kernel(MacroArgs<T> a,
-                                                                    const int32_t *out_y0,
-                                                                    const int32_t *out_y1,
-                                                                    int n_out, double *out) {
-    // Workgroup k < n_out: outlet k, one wave (the others leave), its rows
-    // read 64 at once; workgroup n_out: the inlet and all outlet cells
-    // (boundary_ends).  The sums take the rows in increasing y, one row at a
-    // time, so every sum has the order of a sequential loop.
-    const int k = blockIdx.x, lane = threadIdx.x;
-    auto moments = [&](size_t n, double &rho, double &jx) {
-        double d[9];
+// Boundary sums (lbm_boundary.h) of the stored state (a.fin) and of the state
+// one step later; out: the stored state's 2 n_out + 5 sums, then the later's.
+template <class Cell, bool BC>
+__global__ __launch_bounds__(kBoundaryThreads) void boundary_kernel(
+    SweepArgs<typename Cell::T> a, const int32_t *out_y0, const int32_t *out_y1, int n_out,
+    double *out) {
+    using T = typename Cell::T;
+    auto moments = [](const T (&v)[9], double &rho, double &jx) {
+        double d[9], dr, jy;
 #pragma unroll
-        for (int i = 0; i < 9; ++i) d[i] = Sto<T>::to_d(a.f[(size_t)i * a.plane + n]);
-        double dr, jy;
+        for (int i = 0; i < 9; ++i) d[i] = Sto<T>::to_d(v[i]);
         moments_sym(d, dr, jx, jy);
         rho = 1.0 + dr;
     };
-    if (k < n_out) {
-        if (threadIdx.x >= 64) return;  // one wave per outlet
-        const int y0 = out_y0[k], y1 = out_y1[k];
-        double fl = 0.0, rs = 0.0;
-        for (int c = y0; c <= y1; c += 64) {
-            double r = 0.0, j = 0.0;
-            if (c + lane <= y1) moments((size_t)(c + lane) * a.pitch + (a.nx - 1), r, j);
-            const int m = min(64, y1 - c + 1);
-            for (int t = 0; t < m; ++t) {
-                fl += __shfl(j, t, 64);
-                rs += __shfl(r, t, 64);
-            }
-        }
-        if (lane == 0) {
-            out[k] = fl;
-            out[n_out + k] = rs;
-        }
-    } else {
-        double o[5];
-        boundary_ends(a.cell, a.nx, a.ny, a.pitch,
-                      [&](size_t n, double &rho, double &jx) { moments(n, rho, jx); }, o);
-        if (lane == 0)
+    if (blockIdx.y == 0)
+        boundary_sums(a.cell, a.nx, a.ny, a.pitch, out_y0, out_y1, n_out, out,
+                      [&](int x, int y, double &rho, double &jx) {
+                          const size_t n = (size_t)y * a.pitch + x;
+                          T v[9];
 #pragma unroll
-            for (int q = 0; q < 5; ++q) out[2 * n_out + q] = o[q];
-    }
+                          for (int i = 0; i < 9; ++i) v[i] = a.fin[(size_t)i * a.plane + n];
+                          moments(v, rho, jx);
+                      });
+    else
+        boundary_sums(a.cell, a.nx, a.ny, a.pitch, out_y0, out_y1, n_out, out + 2 * n_out + 5,
+                      [&](int x, int y, double &rho, double &jx) {
+                          typename Cell::CT f[9];
+                          double m, ux, uy;
+                          sweep::step_cell<Cell, BC>(a, x, y, a.cell[(size_t)y * a.pitch + x], f,
+                                                     m, ux, uy);
+                          T v[9];
+#pragma unroll
+                          for (int i = 0; i < 9; ++i) v[i] = Cell::store(f[i]);
+                          moments(v, rho, jx);
+                      });
 }
 
 // ---------------------------------------------------------------------------
@@ -538,6 +525,19 @@ static inline dim3 grid_cells(int ncols, int ny) {
     hipError_t launch_march<T>(const SweepArgs<T> &a, const MarchPlan &p, bool check,    \
                                hipStream_t s) {                                          \
         return sweep::launch_march<CELL>(a, p, check, s);                                \
+    }                                                                                    \
+    template <>                                                                          \
+    hipError_t launch_boundary<T>(const SweepArgs<T> &a, const int32_t *y0,              \
+                                  const int32_t *y1, int n_out, double *out,             \
+                                  hipStream_t s) {                                       \
+        const dim3 g((unsigned)(n_out + 1), 2), b(kBoundaryThreads);                     \
+        if (a.flags)                                                                     \
+            hipLaunchKernelGGL((boundary_kernel<CELL, true>), g, b, 0, s, a, y0, y1,     \
+                               n_out, out);                                              \
+        else                                                                             \
+            hipLaunchKernelGGL((boundary_kernel<CELL, false>), g, b, 0, s, a, y0, y1,    \
+                               n_out, out);                                              \
+        return hipGetLastError();                                                        \
     }
 LBM_OFFSET_LAUNCHERS(float, F32Cell)
 LBM_OFFSET_LAUNCHERS(h16, H16Cell)
@@ -573,15 +573,6 @@ template <typename T>
 hipError_t launch_mass(const MacroArgs<T> &a, double *partials, hipStream_t s) {
     hipLaunchKernelGGL(mass_kernel<T>, grid_cells(a.nx, a.ny), dim3(64, 4), 0,
                        s, a, partials);
-    return hipGetLastError();
-}
-
-template <typename T>
-hipError_t launch_boundary(const MacroArgs<T> &a, const int32_t *y0,
-                           const int32_t *y1, int n_out, double *out,
-                           hipStream_t s) {
-    hipLaunchKernelGGL(boundary_kernel<T>, dim3((unsigned)(n_out + 1)), dim3(kBoundaryThreads),
-                       0, s, a, y0, y1, n_out, out);
     return hipGetLastError();
 }
 
@@ -730,8 +721,6 @@ template hipError_t launch_digest<bf16>(const bf16 *, const uint16_t *, const ui
 #define LBM_OFFSET_INST(T)                                                                  \
     template hipError_t launch_macro<T>(const MacroArgs<T> &, hipStream_t);                  \
     template hipError_t launch_mass<T>(const MacroArgs<T> &, double *, hipStream_t);         \
-    template hipError_t launch_boundary<T>(const MacroArgs<T> &, const int32_t *,            \
-                                           const int32_t *, int, double *, hipStream_t);     \
     template hipError_t launch_export_plane<T>(const T *, const uint16_t *, double *, int,   \
                                                int, int, int, size_t, hipStream_t);          \
     template hipError_t launch_import_plane<T>(T *, const uint16_t *, const double *, int,   \

@@ -255,8 +255,43 @@ __device__ __forceinline__ void check_terms(const SweepArgs<T> &a, size_t n,
     a.uprev[a.plane + n] = uy;
 }
 
-// One time step of the 64 x 4 cells of block (bx, by).  BC: the lattice has
-// boundary-variant cells (flags != 0); without them those paths compile out.
+// One time step of the non-solid cell (x, y) with cell word cw: its populations
+// after the step in f, with the density and velocity of the update.  BC: the
+// lattice has boundary-variant cells (flags != 0); without them those paths
+// compile out.
+template <class Cell, bool BC>
+__device__ __forceinline__ void step_cell(const SweepArgs<typename Cell::T> &a, const int x,
+                                          const int y, const uint32_t cw,
+                                          typename Cell::CT (&f)[9], double &mass, double &ux,
+                                          double &uy) {
+    using CT = typename Cell::CT;
+    const size_t P = a.plane, n = (size_t)y * a.pitch + x;
+    const uint32_t type = update_type(cw);
+    // boundary velocity: the inlet profile, or a Neumann outlet's neighbour
+    CT bx = type == kInlet ? (CT)a.uin[y] : CT(0), by = CT(0);
+    if (BC && type == kOutletNeumann && (cw & kWordLeftLive)) {
+        CT g[9];
+#pragma unroll
+        for (int i = 0; i < 9; ++i) g[i] = Cell::load(a.fin[(size_t)i * P + n - 1]);
+        Cell::velocity(g, bx, by);
+    }
+    if (BC && (cw & kWordGeneral)) {
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            f[i] = Cell::load(a.fin[general_src(cw, i, x, y, y, a.ny, a.flags, P, a.pitch)]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            const bool wall = i > 0 && ((cw >> (i - 1)) & 1u);
+            const size_t src = wall ? (size_t)kOpp[i] * P + n
+                                    : (size_t)i * P + n - kCx[i] - (ptrdiff_t)kCy[i] * a.pitch;
+            f[i] = Cell::load(a.fin[src]);
+        }
+    }
+    Cell::update(f, type, bx, by, a, mass, ux, uy);
+}
+
+// One time step of the 64 x 4 cells of block (bx, by).
 template <class Cell, bool CHECK, bool BC>
 __device__ __forceinline__ void step_body(const SweepArgs<typename Cell::T> &a, const int bx,
                                           const int by, double *part_out) {
@@ -266,36 +301,13 @@ __device__ __forceinline__ void step_body(const SweepArgs<typename Cell::T> &a, 
     const bool in = x < a.nx && y < a.ny;
     const size_t n = (size_t)(in ? y : 0) * a.pitch + (in ? x : 0);
     const uint32_t cw = in ? a.cell[n] : 0u;
-    const uint32_t type = update_type(cw);
     double part[4] = {0.0, 0.0, 0.0, 0.0};
-    if (in && type != kSolid) {
-        const size_t P = a.plane;
-        // boundary velocity: the inlet profile, or a Neumann outlet's neighbour
-        CT bx = type == kInlet ? (CT)a.uin[y] : CT(0), by = CT(0);
-        if (BC && type == kOutletNeumann && (cw & kWordLeftLive)) {
-            CT g[9];
-#pragma unroll
-            for (int i = 0; i < 9; ++i) g[i] = Cell::load(a.fin[(size_t)i * P + n - 1]);
-            Cell::velocity(g, bx, by);
-        }
+    if (in && cell_type(cw) != kSolid) {
         CT f[9];
-        if (BC && (cw & kWordGeneral)) {
-#pragma unroll
-            for (int i = 0; i < 9; ++i)
-                f[i] = Cell::load(a.fin[general_src(cw, i, x, y, y, a.ny, a.flags, P, a.pitch)]);
-        } else {
-#pragma unroll
-            for (int i = 0; i < 9; ++i) {
-                const bool wall = i > 0 && ((cw >> (i - 1)) & 1u);
-                const size_t src = wall ? (size_t)kOpp[i] * P + n
-                                        : (size_t)i * P + n - kCx[i] - (ptrdiff_t)kCy[i] * a.pitch;
-                f[i] = Cell::load(a.fin[src]);
-            }
-        }
         double mass, ux, uy;
-        Cell::update(f, type, bx, by, a, mass, ux, uy);
+        step_cell<Cell, BC>(a, x, y, cw, f, mass, ux, uy);
 #pragma unroll
-        for (int i = 0; i < 9; ++i) a.fout[(size_t)i * P + n] = Cell::store(f[i]);
+        for (int i = 0; i < 9; ++i) a.fout[(size_t)i * a.plane + n] = Cell::store(f[i]);
         if (CHECK) check_terms(a, n, mass, ux, uy, part);
     }
     if (CHECK) {
