@@ -617,6 +617,39 @@ size_t resident_tiles(const lbm_handle *h, int variant) {
     return (size_t)h->cus * std::max<size_t>(1, h->lds_per_cu / std::max<size_t>(lds, 1));
 }
 
+// Region shape of a new lattice (until one is set or tuned): a rule on the
+// precision, the variants and the tile count, never on a size by itself.
+//   float   (32,9) dense while its tiles run in one round of workgroups, since
+//           a launch's fixed cost is then spread over most steps; else, and
+//           with boundary variants, (16,4) dense, of which two workgroups
+//           share a CU.  us per step, compacted (32,8) / (16,4) / (32,9):
+//           256 x 128 distributor 1.43 / 1.24 / 1.21; 773 x 391 1.83 / 1.38 /
+//           1.33; 2200 x 1400 7.05 / 4.51 / 5.47; 1000 x 600 channel 7.23 /
+//           4.41 / 4.84; 360 x 180 half collector 1.91 / 1.51 / 1.75.
+//   16-bit  (16,4) dense: 256 x 128 1.51 / 1.38 / 1.43, 2200 x 1400 7.27 /
+//           4.84 / 6.22.
+//   double  (16,4) dense, but compacted with boundary variants (2.30 against
+//           2.68) and on a few wave rows of cells (128 x 64: 1.74 against
+//           1.96; 773 x 391: 2.33 against 2.23).
+int default_shape(lbm_handle *h) {
+    auto find = [&](int rows, int halo, int kind) {
+        for (int v = 0; v < tb_variant_count(h->precision); ++v) {
+            const TbVariant t = tb_shape(h->precision, v);
+            if (t.rows == rows && t.halo == halo && t.kind == kind) return v;
+        }
+        return 0;
+    };
+    if (h->precision == LBM_F64)
+        return find(16, 4, h->flags != 0 || h->n_nonsolid < 40 * 64 ? kTbCompact : kTbDense);
+    if (h->precision == LBM_F32 && h->flags == 0) {
+        const int v = find(32, 9, kTbDense);
+        if (tile_list(h, tile_width(h->precision, v), tile_height(h->precision, v)).size() <=
+            resident_tiles(h, v))
+            return v;
+    }
+    return find(16, 4, kTbDense);
+}
+
 // After an exchange step: the autotuned shape while its tiles all run in one
 // round of workgroups, else the fastest timed shape whose tiles do (the
 // shape never changes results); see fitted_shape.
@@ -1493,6 +1526,7 @@ int lbm_create_geometry(const lbm_geometry_desc *d, const uint8_t *cell_types,
         with_storage(h->precision, [&](auto t) { reset_all<decltype(t)>(h); });
         HIP_TRY(launch_build_cells(h->types.as<uint8_t>(), h->cell.as<uint16_t>(), h->nx,
                                    h->ny, h->pitch, h->flags, h->stream));
+        h->tb_variant = default_shape(h);
         rebuild_tiles(h);
         h->march = default_march(h);
         HIP_TRY(hipStreamSynchronize(h->stream));

@@ -176,8 +176,8 @@ hipError_t launch_sweep(const SweepArgs<T> &a, bool check, hipStream_t s);
 // cells, 1024 threads per workgroup, two LDS copies of the region
 // (9 * 64 * rows * sizeof(T) bytes each; one copy in the in-place form) and,
 // in the compacted form, a list of the region's non-solid cells (4 bytes per
-// region cell); at most 160 KB in all.  A few shapes are compiled per storage type; variant 0 is the
-// default, the autotuner may pick another.  The shape never changes the
+// region cell); at most 160 KB in all.  A few shapes are compiled per storage type; a lattice
+// starts with one chosen by a rule, the autotuner may pick another.  The shape never changes the
 // results, only the speed.
 // Region bodies: dense (a lane per region column), compacted (lanes take
 // consecutive entries of a list of the region's non-solid cells), or dense
