@@ -102,13 +102,15 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], int tid,
 
 // ---------------------------------------------------------------------------
 // One cell of one time step on offsets d_i = f_i - w_i stored as T (float,
-// or 16-bit for the reduced-storage forms), arithmetic in CT (all forms:
-// float).  Zou-He closure on inlet
+// or 16-bit for the reduced-storage forms), arithmetic in CT (all
+// forms: float).  The relaxation restores exact mass
+// and momentum conservation after rounding (see update); without that, the
+// rounded weights bias every step the same way and float arithmetic, not
+// the storage, dominated the error of steady fields.  Zou-He closure on inlet
 // (velocity u_in, unknowns 1, 5, 8) and outlet cells (density rho_out, zero
 // transverse velocity, unknowns 3, 6, 7), moments (Eq. 2), BGK relaxation
-// (Eq. 1) to the equilibrium of Sec. 2.1 written for offsets,
-// feq_i - w_i = w_i (drho + rho (3 c.u + 4.5 (c.u)^2 - 1.5 u.u)), in moment
-// form, conserving mass and momentum by construction (see update).  Every sum
+// (Eq. 1) to the equilibrium of Sec. 2.1 written for offsets:
+// feq_i - w_i = w_i (drho + rho (3 c.u + 4.5 (c.u)^2 - 1.5 u.u)).  Every sum
 // pairs the populations that a reflection y -> -y exchanges (2<->4, 5<->8,
 // 6<->7) and every product maps to itself or its exact negative under it, so
 // on a mirror-symmetric lattice the computed flow is mirror-symmetric bit for
@@ -202,58 +204,51 @@ struct OffsetCell {
     __device__ static __forceinline__ void relax(CT (&d)[9], const SweepArgs<T> &a, double &mass,
                                                  double &ux_out, double &uy_out) {
 #pragma clang fp contract(on)
-        // The relaxation in moment form.  The sums and differences of opposite
-        // populations (a: 1 +- 3, b: 2 +- 4) and of the four diagonal ones
-        // are, up to factors, nine moments: density, the two momenta, and six
-        // others, whose equilibria are short polynomials of
-        //   xx = rho ux^2, yy = rho uy^2, xy = rho ux uy
-        // (the equilibrium of Sec. 2.1 summed over the same combinations):
-        //   1+3: 2/9 dr + xx - (xx + yy)/3     1-3: 2/3 jx
-        //   2+4: 2/9 dr + yy - (xx + yy)/3     2-4: 2/3 jy
-        //   5+6+7+8: 1/9 dr + (xx + yy)/3      5-6+7-8: xy
-        // One relaxation time, so each combination's increment t = e - m is
-        // spread back onto its populations with factors 1/2 and 1/4.  Mass
-        // and momentum are conserved by construction: the rest population
-        // takes minus the sum of the even increments, the diagonals' momenta
-        // minus the axis ones.  (With increments formed population by
-        // population, the rounded weights leave a defect of ~1e-8 relative
-        // with a fixed sign at every step, which the flow's slowest mode
-        // accumulates to ~1e-4 over thousands of steps.)  Every coefficient is
-        // formed from the one rounded weight w = 1/9: with 2/3 and 1/3 rounded
-        // by themselves, four times further off, u_y of the 1024 x 512
-        // distributor after 20,000 steps was 1.0-1.4e-6 off in place of
-        // 0.44-0.48e-6 (population by population 0.51-0.54e-6).
-        // The update is nearly all of the blocked sweeps' vector instructions,
-        // 59 per fluid cell here
-        // against 89 population by population.  1024 x 512 distributor, 20,000
-        // steps: 32.9 -> 30.0 ms; 1024 x 512 channel, 4000 steps: 18.9 -> 18.1
-        // ms; 48 candidates in a batch, 1000 steps: 23.0 -> 21.8 ms.
-        const CT a1 = d[1] + d[3], b1 = d[1] - d[3], a2 = d[2] + d[4], b2 = d[2] - d[4];
-        const CT p = d[5] + d[8], q = d[6] + d[7], r = d[5] - d[8], s = d[6] - d[7];
-        const CT ad = p + q, bx5 = p - q, by5 = r + s, cd = r - s;
-        const CT dr = (d[0] + a1) + (a2 + ad);
-        const CT jx = b1 + bx5, jy = b2 + by5;
-        const CT ir = recip(CT(1) + dr);
+        const CT dr = ((d[0] + (d[1] + d[3])) + (d[2] + d[4])) + ((d[5] + d[8]) + (d[6] + d[7]));
+        const CT rho = CT(1) + dr;
+        const CT jx = (d[1] + (d[5] + d[8])) - (d[3] + (d[6] + d[7]));
+        const CT jy = (d[2] + (d[5] + d[6])) - (d[4] + (d[8] + d[7]));
+        const CT ir = recip(rho);
         const CT ux = jx * ir, uy = jy * ir;
-        const CT xx = jx * ux, yy = jy * uy;
-        const CT w = CT(1) / CT(9), e3 = CT(3) * (xx + yy), j3 = CT(3) * jx, k3 = CT(3) * jy;
-        const CT ta1 = (CT(2) * w * dr - a1) + (xx - w * e3);
-        const CT ta2 = (CT(2) * w * dr - a2) + (yy - w * e3);
-        const CT tad = w * e3 + (w * dr - ad);
-        const CT tb1 = bx5 - w * j3, tb2 = by5 - w * k3;
-        const CT tcd = jx * uy - cd;
-        const CT om = (CT)a.omega, om2 = CT(0.5) * om, om4 = CT(0.25) * om;
-        d[0] = d[0] - om * ((ta1 + ta2) + tad);
-        d[1] = d[1] + om2 * (ta1 + tb1);
-        d[3] = d[3] + om2 * (ta1 - tb1);
-        d[2] = d[2] + om2 * (ta2 + tb2);
-        d[4] = d[4] + om2 * (ta2 - tb2);
-        const CT tp = tad - tb1, tq = tad + tb1;    // 2 (t5 + t8), 2 (t6 + t7)
-        const CT tr = tcd - tb2, ts = tcd + tb2;    // 2 (t5 - t8), -2 (t6 - t7)
-        d[5] = d[5] + om4 * (tp + tr);
-        d[8] = d[8] + om4 * (tp - tr);
-        d[6] = d[6] + om4 * (tq - ts);
-        d[7] = d[7] + om4 * (tq + ts);
+        const CT om = (CT)a.omega;
+        // Opposite directions i, opp(i) have c.u = +-cu: their equilibrium
+        // offsets share the even part A = 4.5 cu^2 - 1.5 u.u and differ in the
+        // sign of the odd part B = 3 cu.
+        const CT pux = ux, puy = uy;
+        const CT puu15 = CT(1.5) * (pux * pux + puy * puy);
+        // With the weights rounded (to float), the equilibrium's mass and
+        // momentum differ from dr and (jx, jy) by ~1e-8 relative, every step,
+        // with a fixed sign: a bias that the flow's slowest mode accumulates
+        // over thousands of steps (a steady-state error ~1e-4).  So the
+        // increments t_i = e_i - d_i toward equilibrium are corrected to
+        // conserve exactly before the relaxation: the (1,3) and (2,4) pairs
+        // take the momentum defects, t_0 the mass defect.  Each population
+        // then relaxes as d_i + om t_i in one multiply-add.  Every sum is in
+        // mirror-symmetric order, so a y-reflection maps each increment onto
+        // its mirror image bit for bit.
+        CT t[9];
+        // A + B = (4.5 cu + 3) cu - 1.5 u.u and A - B = (4.5 cu - 3) cu - 1.5 u.u,
+        // two multiply-adds each.
+        auto incr_pair = [&](int i, int j, CT cu, CT w) {
+            const CT hp = CT(4.5) * cu + CT(3), hm = CT(4.5) * cu - CT(3);
+            const CT ApB = hp * cu - puu15, AmB = hm * cu - puu15;
+            t[i] = w * (dr + rho * ApB) - d[i];
+            t[j] = w * (dr + rho * AmB) - d[j];
+        };
+        const CT w1 = CT(1) / CT(9), w5 = CT(1) / CT(36);
+        incr_pair(1, 3, pux, w1);
+        incr_pair(2, 4, puy, w1);
+        incr_pair(5, 7, pux + puy, w5);
+        incr_pair(6, 8, puy - pux, w5);
+        const CT mx = (t[1] - t[3]) + ((t[5] - t[7]) + (t[8] - t[6]));
+        const CT my = (t[2] - t[4]) + ((t[5] - t[8]) + (t[6] - t[7]));
+        t[1] = t[1] - CT(0.5) * mx;
+        t[3] = t[3] + CT(0.5) * mx;
+        t[2] = t[2] - CT(0.5) * my;
+        t[4] = t[4] + CT(0.5) * my;
+        t[0] = -(((t[1] + t[3]) + (t[2] + t[4])) + ((t[5] + t[8]) + (t[6] + t[7])));
+#pragma unroll
+        for (int i = 0; i < 9; ++i) d[i] = d[i] + om * t[i];
         mass = 1.0 + (double)dr;
         ux_out = (double)ux;
         uy_out = (double)uy;
