@@ -743,7 +743,9 @@ MacroArgs<T> macro_args(lbm_handle *h) {
 
 // Lattices of at least this many cells march untuned: below, a segment has too
 // few rows for what it advances beyond its ends.  us per step against the
-// best region shape, all-fluid channels, FP32: 1024 x 512 4.6 against 4.0,
+// best region shape, all-fluid channels, timed with a shorter float update on
+// both sides (now 2000 steps of 4096 x 2048 take 97 ms against 148 blocked,
+// 2000 x 1000 FP16 28 against 36, read-back included), FP32: 1024 x 512 4.6 against 4.0,
 // 1400 x 700 5.9 against 6.3, 1700 x 850 6.8 against 8.4, 2300 x 2000 15.6
 // against 29.3; FP16: 1400 x 700 6.7 against 6.8, 2300 x 2000 18.6 against
 // 27.6; FP64: 700 x 350 6.1 against 5.3, 1024 x 512 7.7 against 8.2, 1400 x

@@ -360,7 +360,8 @@ __global__ __launch_bounds__(256) void step_batch_kernel(
 // its cells has the depth: what the lanes beyond it compute is never read by
 // a valid cell, and solid cells are never read at all, so neither the pulls
 // nor the stores need a lane mask; only the tile's cells are written to HBM.
-// us per launch against lane masks and nine populations in LDS: 1024 x 512
+// us per launch against lane masks and nine populations in LDS (both with an
+// update of 57 instructions, since taken back): 1024 x 512
 // distributor, (32,9), 12.2 -> 11.9; 1024 x 512 channel, (16,4), 15.9 -> 15.4
 // and (32,8) 34.2 -> 32.4; 256 x 128 distributor, (32,9), 11.9 -> 10.6.
 // Reading both of a wave's rows before relaxing either was slower (12.1,
