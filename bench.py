@@ -74,12 +74,6 @@ MEASURED_TRAFFIC_PER_FULL_LAUNCH = {
     ("channel-1024x512", "f32", 1): 43.170e6,
     ("channel-1024x512", "f32", 0): 43.250e6,
     ("channel-1024x512", "f32", 5): 44.016e6,
-    # profiles/sweep_tb_float_channel-4096x2048.txt, the same shapes
-    ("channel-4096x2048", "f32", 4): 637.188e6,
-    ("channel-4096x2048", "f32", 3): 640.631e6,
-    ("channel-4096x2048", "f32", 1): 935.983e6,
-    ("channel-4096x2048", "f32", 0): 936.164e6,
-    ("channel-4096x2048", "f32", 5): 1027.100e6,
 }
 # The same for the batched kernel, per launch, keyed by (workload, storage,
 # shape, order).
@@ -442,27 +436,23 @@ def bench_serve(args) -> int:
 
 
 # Vector ALU instructions (wave instructions, rocprofv3 SQ_INSTS_VALU) of one
-# full launch of the blocked sweep, keyed like the traffic table, from the
-# same profiles.  Each wave instruction occupies a SIMD for 4 cycles (64
-# lanes on 16-wide SIMDs; packed FP32 is not used), so the chip issues at
-# most 256 CUs x 4 SIMDs x 2.4 GHz / 4 = 614.4 G wave instructions per second.
+# full launch of the blocked sweep, keyed like the traffic table.  (Lattices
+# that march, such as the 4096x2048 channel, have no entry.)  An FP32 wave
+# instruction was measured to occupy a SIMD for 2.3-2.8 cycles, so the chip
+# issues at most about 256 CUs x 4 SIMDs x 2.4 GHz / 2 = 1,228.8 G wave
+# instructions per second (FP64: 4.6-5.3 cycles, half of that).
 MEASURED_VALU_PER_FULL_LAUNCH = {
-    ("distributor-1024x512-L3", "f32", 5): 3.937e6,
-    ("distributor-1024x512-L3", "f32", 1): 3.455e6,
-    ("distributor-1024x512-L3", "f32", 0): 3.218e6,
-    ("distributor-1024x512-L3", "f64", 3): 5.611e6,
-    ("distributor-1024x512-L3", "f64", 1): 2.433e6,
-    ("distributor-1024x512-L3", "f64", 0): 2.240e6,
-    ("channel-1024x512", "f32", 4): 8.107e6,
-    ("channel-1024x512", "f32", 3): 9.306e6,
-    ("channel-1024x512", "f32", 1): 15.07e6,
-    ("channel-1024x512", "f32", 0): 16.11e6,
-    ("channel-1024x512", "f32", 5): 19.17e6,
-    ("channel-4096x2048", "f32", 4): 125.8e6,
-    ("channel-4096x2048", "f32", 3): 146.8e6,
-    ("channel-4096x2048", "f32", 1): 235.3e6,
-    ("channel-4096x2048", "f32", 0): 256.4e6,
-    ("channel-4096x2048", "f32", 5): 296.9e6,
+    ("distributor-1024x512-L3", "f32", 5): 4.062e6,
+    ("distributor-1024x512-L3", "f32", 1): 3.573e6,
+    ("distributor-1024x512-L3", "f32", 0): 3.226e6,
+    ("distributor-1024x512-L3", "f64", 3): 4.081e6,
+    ("distributor-1024x512-L3", "f64", 1): 1.927e6,
+    ("distributor-1024x512-L3", "f64", 0): 1.839e6,
+    ("channel-1024x512", "f32", 4): 8.234e6,
+    ("channel-1024x512", "f32", 3): 9.328e6,
+    ("channel-1024x512", "f32", 1): 15.39e6,
+    ("channel-1024x512", "f32", 0): 16.19e6,
+    ("channel-1024x512", "f32", 5): 19.60e6,
 }
 # The same for the batched kernel, per launch, keyed by (workload, storage,
 # shape, order) like MEASURED_TRAFFIC_PER_LAUNCH.
@@ -479,7 +469,7 @@ MEASURED_VALU_PER_LAUNCH = {
     ("batch-256-candidates", "f32", 6, 1): 43.54e6,
     ("batch-256-candidates", "f32", 6, 0): 43.54e6,
 }
-VALU_PEAK_WAVE_INSTR_PER_S = 256 * 4 * 2.4e9 / 4
+VALU_PEAK_WAVE_INSTR_PER_S = 256 * 4 * 2.4e9 / 2
 
 
 def hbm_and_limiter(roof: dict, traffic, valu, avg_ms: float) -> None:
