@@ -437,10 +437,12 @@ def bench_serve(args) -> int:
 
 # Vector ALU instructions (wave instructions, rocprofv3 SQ_INSTS_VALU) of one
 # full launch of the blocked sweep, keyed like the traffic table.  (Lattices
-# that march, such as the 4096x2048 channel, have no entry.)  An FP32 wave
-# instruction was measured to occupy a SIMD for 2.3-2.8 cycles, so the chip
-# issues at most about 256 CUs x 4 SIMDs x 2.4 GHz / 2 = 1,228.8 G wave
-# instructions per second (FP64: 4.6-5.3 cycles, half of that).
+# that march, such as the 4096x2048 channel, have no entry.)  The limiter's peak
+# is the nominal rate of 64 lanes on 16-wide SIMDs, 4 cycles an instruction: 256
+# CUs x 4 SIMDs x 2.4 GHz / 4 = 614.4 G wave instructions per second.  Measured,
+# an FP32 instruction takes a SIMD 2.3-2.8 cycles with two or more waves on it
+# (FP64 4.6-5.3), so for FP32 the share of what the chip can issue is about
+# half of the fraction reported.
 MEASURED_VALU_PER_FULL_LAUNCH = {
     ("distributor-1024x512-L3", "f32", 5): 4.062e6,
     ("distributor-1024x512-L3", "f32", 1): 3.573e6,
@@ -469,7 +471,7 @@ MEASURED_VALU_PER_LAUNCH = {
     ("batch-256-candidates", "f32", 6, 1): 43.54e6,
     ("batch-256-candidates", "f32", 6, 0): 43.54e6,
 }
-VALU_PEAK_WAVE_INSTR_PER_S = 256 * 4 * 2.4e9 / 2
+VALU_PEAK_WAVE_INSTR_PER_S = 256 * 4 * 2.4e9 / 4
 
 
 def hbm_and_limiter(roof: dict, traffic, valu, avg_ms: float) -> None:
