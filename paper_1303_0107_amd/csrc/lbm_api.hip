@@ -388,15 +388,7 @@ struct lbm_handle {
     int march = 0;              // steps per launch of the marching sweep, 0: blocked sweep
     int march_env = -1;         // LBM_MARCH: 0 never, n >= 1 steps wherever possible, -1 unset
     int64_t check_parts = 0;    // partials of the last check launch
-    // Non-solid cell counts per tile of a tw x th tiling and the tiles that
-    // hold one, row-major, packed (tile row << 16 | tile column); built once
-    // per tiling by a scan of the mask, then kept current from the cells each
-    // exchange step flips.
-    struct Tiling {
-        int tw = 0, th = 0, ntx = 0, nty = 0;
-        std::vector<int32_t> count, list;
-    };
-    std::vector<Tiling> tilings;
+    Tilings tilings;
     int64_t prof_kernels = 0;
     int64_t prof_intervals = 0;  // check intervals seen since profiling was enabled
 
@@ -540,46 +532,9 @@ void compute_ports(lbm_handle *h) {
     }
 }
 
-void list_tiles(lbm_handle::Tiling &t) {
-    t.list.clear();
-    for (int ty = 0; ty < t.nty; ++ty)
-        for (int tx = 0; tx < t.ntx; ++tx)
-            if (t.count[(size_t)ty * t.ntx + tx] > 0) t.list.push_back((ty << 16) | tx);
-}
-
-// Tiles of a tw x th tiling that hold a non-solid cell (cached per tiling).
+// Tiles of a tw x th tiling that hold a non-solid cell (kept from then on).
 const std::vector<int32_t> &tile_list(lbm_handle *h, int tw, int th) {
-    for (const auto &t : h->tilings)
-        if (t.tw == tw && t.th == th) return t.list;
-    lbm_handle::Tiling t;
-    t.tw = tw;
-    t.th = th;
-    t.ntx = (h->nx + tw - 1) / tw;
-    t.nty = (h->ny + th - 1) / th;
-    t.count.assign((size_t)t.ntx * t.nty, 0);
-    for (int y = 0; y < h->ny; ++y) {
-        const uint8_t *row = h->host_types.data() + (size_t)y * h->nx;
-        int32_t *c = t.count.data() + (size_t)(y / th) * t.ntx;
-        for (int tx = 0; tx < t.ntx; ++tx) {
-            int n = 0;
-            const int x1 = std::min(h->nx, (tx + 1) * tw);
-            for (int x = tx * tw; x < x1; ++x) n += row[x] != LBM_SOLID;
-            c[tx] += n;
-        }
-    }
-    list_tiles(t);
-    h->tilings.push_back(std::move(t));
-    return h->tilings.back().list;
-}
-
-// Cells made solid (removed) and fluid (added) by an exchange step.
-void tilings_flip(lbm_handle *h, const std::vector<int32_t> &removed,
-                  const std::vector<int32_t> &added) {
-    for (auto &t : h->tilings) {
-        for (int32_t n : removed) --t.count[(size_t)((n / h->nx) / t.th) * t.ntx + (n % h->nx) / t.tw];
-        for (int32_t n : added) ++t.count[(size_t)((n / h->nx) / t.th) * t.ntx + (n % h->nx) / t.tw];
-        list_tiles(t);
-    }
+    return h->tilings.list(h->host_types.data(), h->nx, h->ny, tw, th);
 }
 
 // Tiles of the temporal-blocking sweep (current shape) whose cells include a
@@ -617,37 +572,17 @@ size_t resident_tiles(const lbm_handle *h, int variant) {
     return (size_t)h->cus * std::max<size_t>(1, h->lds_per_cu / std::max<size_t>(lds, 1));
 }
 
-// Region shape of a new lattice (until one is set or tuned): a rule on the
-// precision, the variants and the tile count, never on a size by itself.
-//   float   (32,9) dense while its tiles run in one round of workgroups, since
-//           a launch's fixed cost is then spread over most steps; else, and
-//           with boundary variants, (16,4) dense, of which two workgroups
-//           share a CU.  us per step, compacted (32,8) / (16,4) / (32,9):
-//           256 x 128 distributor 1.43 / 1.24 / 1.21; 773 x 391 1.83 / 1.38 /
-//           1.33; 2200 x 1400 7.05 / 4.51 / 5.47; 1000 x 600 channel 7.23 /
-//           4.41 / 4.84; 360 x 180 half collector 1.91 / 1.51 / 1.75.
-//   16-bit  (16,4) dense: 256 x 128 1.51 / 1.38 / 1.43, 2200 x 1400 7.27 /
-//           4.84 / 6.22.
-//   double  (16,4) dense, but compacted with boundary variants (2.30 against
-//           2.68) and on a few wave rows of cells (128 x 64: 1.74 against
-//           1.96; 773 x 391: 2.33 against 2.23).
+// Region shape of a new lattice (until one is set or tuned).
 int default_shape(lbm_handle *h) {
-    auto find = [&](int rows, int halo, int kind) {
-        for (int v = 0; v < tb_variant_count(h->precision); ++v) {
-            const TbVariant t = tb_shape(h->precision, v);
-            if (t.rows == rows && t.halo == halo && t.kind == kind) return v;
-        }
-        return 0;
-    };
-    if (h->precision == LBM_F64)
-        return find(16, 4, h->flags != 0 || h->n_nonsolid < 40 * 64 ? kTbCompact : kTbDense);
-    if (h->precision == LBM_F32 && h->flags == 0) {
-        const int v = find(32, 9, kTbDense);
-        if (tile_list(h, tile_width(h->precision, v), tile_height(h->precision, v)).size() <=
-            resident_tiles(h, v))
-            return v;
+    const int n = tb_variant_count(h->precision);
+    std::vector<TbVariant> shapes(n);
+    std::vector<size_t> resident(n);
+    for (int v = 0; v < n; ++v) {
+        shapes[v] = tb_shape(h->precision, v);
+        resident[v] = resident_tiles(h, v);
     }
-    return find(16, 4, kTbDense);
+    return start_shape(shapes, resident, (int)h->esize(), h->flags != 0, h->n_nonsolid,
+                       h->host_types.data(), h->nx, h->ny);
 }
 
 // After an exchange step: the autotuned shape while its tiles all run in one
@@ -1998,7 +1933,7 @@ void exchange_finish(Exchange &e) {
     h->last_removed.assign(rem.begin(), rem.end());
     h->last_added.assign(add.begin(), add.end());
     if (keff > 0) {
-        tilings_flip(h, rem, add);
+        h->tilings.flip(h->nx, rem, add);
         rebuild_tiles(h);
         refit_shape(h);
         ++h->mask_version;

@@ -8,6 +8,8 @@
 
 #include <type_traits>
 
+#include "lbm_tiles.h"
+
 struct lbm_handle;
 
 namespace lbm {
@@ -179,13 +181,7 @@ hipError_t launch_sweep(const SweepArgs<T> &a, bool check, hipStream_t s);
 // region cell); at most 160 KB in all.  A few shapes are compiled per storage type; a lattice
 // starts with one chosen by a rule, the autotuner may pick another.  The shape never changes the
 // results, only the speed.
-// Region bodies: dense (a lane per region column), compacted (lanes take
-// consecutive entries of a list of the region's non-solid cells), or dense
-// with one region copy updated in place (half the LDS, so taller regions).
-enum TbKind : int { kTbDense = 0, kTbCompact = 1, kTbInPlace = 2 };
-struct TbVariant {
-    int rows, halo, kind;
-};
+// (Bodies and shapes: TbKind and TbVariant, lbm_tiles.h.)
 template <typename T>
 struct TbVariants;
 template <>
