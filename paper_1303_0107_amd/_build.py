@@ -26,6 +26,9 @@ COMMON = [
 # operation rounds once, in the order written).
 SOURCES = {
     "lbm_kernels.hip": [],
+    "lbm_march_f32.hip": [],
+    "lbm_march_f16.hip": [],
+    "lbm_march_bf16.hip": [],
     "lbm_f64.hip": ["-ffp-contract=off"],
     "lbm_api.hip": ["-ffp-contract=off"],
     "lbm_serve.hip": [],
