@@ -83,7 +83,8 @@ __device__ __forceinline__ void block_sum(double (&v)[NV], int tid) {
 // reciprocal could leave the normal range, so those waves divide.  A quotient
 // below 2^-500 may differ in its last place; it is lost entirely in the sums
 // 1 + 3 c.u and in the squares it enters.  Eleven instructions for the pair,
-// the two divisions take 22.
+// the two divisions take 22.  (Lanes relaxed without a cell of their own are
+// kept near rest, so that they do not decide the vote.)
 __device__ __forceinline__ void divide_pair(double a, double b, double r, double &qa,
                                             double &qb) {
     // biased exponent of r within 512 of that of 1, and r positive
@@ -109,6 +110,7 @@ __device__ __forceinline__ void divide_pair(double a, double b, double r, double
 struct Cell {
     using T = double;
     using CT = ArithT<double>;
+    static constexpr bool kOffsets = false;
     __device__ static __forceinline__ double load(double v) { return v; }
     __device__ static __forceinline__ double store(double v) { return v; }
     // Velocity (Eq. 2) of a stored population set, formed as the oracle does.

@@ -38,6 +38,7 @@ template <typename Storage, typename Arith>
 struct OffsetCell {
     using T = Storage;
     using CT = Arith;
+    static constexpr bool kOffsets = true;
     __device__ static __forceinline__ CT load(T v) { return (CT)Sto<T>::to_d(v); }
     __device__ static __forceinline__ CT load_f(T v) { return (CT)Sto<T>::to_f(v); }
     __device__ static __forceinline__ T store(CT v) {

@@ -34,13 +34,11 @@
 #include <type_traits>
 
 #include "lbm_internal.h"
+#include "lbm_lanes.h"
 
 namespace lbm {
 namespace sweep {
 
-__device__ constexpr int kCx[9] = {0, 1, 0, -1, 0, 1, -1, -1, 1};
-__device__ constexpr int kCy[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
-__device__ constexpr int kOpp[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
 // mirror image of c_i under y -> -y
 __device__ constexpr int kMirY[9] = {0, 1, 4, 3, 2, 8, 7, 6, 5};
 
@@ -360,6 +358,13 @@ __global__ __launch_bounds__(256) void step_batch_kernel(
 // its cells has the depth: what the lanes beyond it compute is never read by
 // a valid cell, and solid cells are never read at all, so neither the pulls
 // nor the stores need a lane mask; only the tile's cells are written to HBM.
+// The lanes without a cell start from rest and pull as the others do
+// (lbm_lanes.h).  Pulling from their own place, and starting from zero, they
+// met their neighbours' banks (620,000 conflict cycles in a launch on the 1024
+// x 512 FP32 channel, 17,000 so) and their zero density sent every FP64 wave
+// row with a solid or off-lattice lane to the divisions: FP64 (16,4) us per
+// step 1.92 -> 1.82 (256 x 128 distributor), 9.17 -> 8.95 (1024 x 512
+// channel); FP16 (16,4) 2 % less on average over 24 lattices.
 // us per launch against lane masks and nine populations in LDS (both with an
 // update of 57 instructions, since taken back): 1024 x 512
 // distributor, (32,9), 12.2 -> 11.9; 1024 x 512 channel, (16,4), 15.9 -> 15.4
@@ -419,7 +424,8 @@ __device__ __forceinline__ void tb_body(const SweepArgs<typename Cell::T> &a, co
             for (int i = 0; i < 9; ++i) v[c][i] = p[(size_t)i * a.plane];
         } else {
 #pragma unroll
-            for (int i = 0; i < 9; ++i) v[c][i] = Cell::store(CT(0));
+            for (int i = 0; i < 9; ++i)
+                v[c][i] = Cell::store((CT)idle_population(Cell::kOffsets, i));
         }
     }
 #pragma unroll
@@ -430,11 +436,7 @@ __device__ __forceinline__ void tb_body(const SweepArgs<typename Cell::T> &a, co
 #pragma unroll
         for (int i = 1; i < 9; ++i) {
             L[2 * i * PL + pos] = v[c][i];
-            // a wall's pull, and the unused ones of the region's edge, are the
-            // cell's own
-            const bool wall = ((cw[c] >> (i - 1)) & 1u) || depth[c] == 0;
-            const int e = wall ? 2 * kOpp[i] * PL + pos : 2 * i * PL + pos - kCy[i] * RW - kCx[i];
-            src[c][i] = L + e;
+            src[c][i] = L + pull_entry(cw[c], i, pos, PL, RW);
         }
         dst[c].set(L, pos);
         reach[c] = 0;
