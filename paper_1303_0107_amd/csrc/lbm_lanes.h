@@ -41,5 +41,26 @@ LBM_LANE_FN double idle_population(bool offsets, int i) {
     return offsets ? 0.0 : i == 0 ? 4.0 / 9.0 : i < 5 ? 1.0 / 9.0 : 1.0 / 36.0;
 }
 
+// The 64 lanes' flags in the opposite order.
+LBM_LANE_FN uint64_t mirrored(uint64_t lanes) {
+#if defined(__HIPCC__)
+    return __builtin_bitreverse64(lanes);
+#else
+    uint64_t r = 0;
+    for (int l = 0; l < 64; ++l) r |= (lanes >> l & 1u) << (63 - l);
+    return r;
+#endif
+}
+
+// Largest depth (distance to the region's edge) of a row's cells: row ry of a
+// region of 64 columns and rh rows, `lanes` the columns that hold a cell; 0
+// without one.  Lanes l and 63 - l have the same distance, so the row is
+// folded onto its first half, where the highest column set has the largest.
+LBM_LANE_FN int row_reach(uint64_t lanes, int ry, int rh) {
+    const uint32_t cols = (uint32_t)(lanes | mirrored(lanes));
+    const int col = cols ? 31 - __builtin_clz(cols) : 0, row = ry < rh - 1 - ry ? ry : rh - 1 - ry;
+    return col < row ? col : row;
+}
+
 }  // namespace sweep
 }  // namespace lbm

@@ -365,13 +365,16 @@ __global__ __launch_bounds__(256) void step_batch_kernel(
 // row with a solid or off-lattice lane to the divisions: FP64 (16,4) us per
 // step 1.92 -> 1.82 (256 x 128 distributor), 9.17 -> 8.95 (1024 x 512
 // channel); FP16 (16,4) 2 % less on average over 24 lattices.
-// us per launch against lane masks and nine populations in LDS (both with an
-// update of 57 instructions, since taken back): 1024 x 512
-// distributor, (32,9), 12.2 -> 11.9; 1024 x 512 channel, (16,4), 15.9 -> 15.4
-// and (32,8) 34.2 -> 32.4; 256 x 128 distributor, (32,9), 11.9 -> 10.6.
-// Reading both of a wave's rows before relaxing either was slower (12.1,
-// 33.2), and 67 registers in place of 64 leave the 16-row shapes one
-// workgroup a CU (15.4 -> 20.8).
+// FP32 us per step against lane masks and nine populations in LDS, the same
+// arithmetic on both sides: 1024 x 512 distributor, (32,9), 1.50 -> 1.46; 1024
+// x 512 channel, (16,4), 4.18 -> 4.16 and (32,8) 4.57 -> 4.34; 256 x 128
+// distributor, (32,9), 1.45 -> 1.26.  What a launch does before its first step
+// counts as much as the steps: the deepest cell of a row found by a vote for
+// each depth instead of row_reach costs 4 % of a step on (32,9) and 2 % on the
+// 16-bit (16,4), and initialising the second copy for the lanes that read it
+// unwritten 1.5 %.  Reading both of a wave's rows before relaxing either was
+// slower, and 67 registers in place of 64 leave the 16-row shapes one
+// workgroup a CU (a third slower).
 template <class Cell, int RH, int H, int NT, bool CHECK, bool BC, bool HALT, bool PREV>
 __device__ __forceinline__ void tb_body(const SweepArgs<typename Cell::T> &a, const int t,
                                         const int steps, double *part_out) {
@@ -394,7 +397,7 @@ __device__ __forceinline__ void tb_body(const SweepArgs<typename Cell::T> &a, co
 
     uint32_t cw[CPT];
     int depth[CPT];
-    int reach[CPT];        // largest depth in the row, at most H (the same in every lane)
+    int reach[CPT];        // largest depth in the row (the same in every lane)
     bool closing[CPT];     // the row has inlet or outlet cells (the same in every lane)
     const T *src[CPT][9];  // LDS address of each pull in copy 0
     StoreBases<T, PL> dst[CPT];
@@ -439,10 +442,7 @@ __device__ __forceinline__ void tb_body(const SweepArgs<typename Cell::T> &a, co
             src[c][i] = L + pull_entry(cw[c], i, pos, PL, RW);
         }
         dst[c].set(L, pos);
-        reach[c] = 0;
-#pragma unroll
-        for (int k = 1; k <= H; ++k) reach[c] += __any(depth[c] >= k) ? 1 : 0;
-        reach[c] = __builtin_amdgcn_readfirstlane(reach[c]);
+        reach[c] = row_reach(__ballot(cell_type(cw[c]) != kSolid), wave + c * NW, RH);
         closing[c] = __any(cell_type(cw[c]) > kFluid);
     }
     if (gate.ended(a)) return;

@@ -60,6 +60,14 @@ int main(int argc, char **argv) {
         const int x = n % RW, y = n / RW;
         if (!solid[n]) reach[y] = std::max(reach[y], std::min({x, RW - 1 - x, y, RH - 1 - y}));
     }
+    for (int y = 0; y < RH; ++y) {
+        uint64_t lanes = 0;
+        for (int x = 0; x < RW; ++x) lanes |= (uint64_t)!solid[y * RW + x] << x;
+        if (row_reach(lanes, y, RH) != reach[y]) {
+            std::printf("row %d reach %d for %d\n", y, row_reach(lanes, y, RH), reach[y]);
+            return 0;
+        }
+    }
     double lo = 1.0, hi = 1.0;
     for (int s = 1; s <= H; ++s) {
         const int B = (s - 1) & 1;
@@ -159,3 +167,40 @@ def test_lanes_without_a_cell_stay_near_rest(region, rows, halo, solid, stripes,
     inside a factor of two."""
     lo, hi = region(rows, halo, 3, solid, stripes, offsets)
     assert 0.5 < lo <= hi < 2.0
+
+
+REACH = r"""
+#include <algorithm>
+#include <cstdio>
+#include "lbm_lanes.h"
+// Every row of one or two cells, in each row of a region.
+int main() {
+    for (int rh : {16, 32})
+        for (int ry = 0; ry < rh; ++ry)
+            for (int a = 0; a <= 64; ++a)
+                for (int b = a; b <= 64; ++b) {
+                    uint64_t lanes = 0;
+                    int want = 0;
+                    for (int x : {a, b})
+                        if (x < 64) {
+                            lanes |= 1ull << x;
+                            want = std::max(want, std::min({x, 63 - x, ry, rh - 1 - ry}));
+                        }
+                    if (lbm::sweep::row_reach(lanes, ry, rh) != want)
+                        return std::printf("%d %d %d %d\n", rh, ry, a, b), 1;
+                }
+    return 0;
+}
+"""
+
+
+def test_row_reach_is_the_deepest_cell(tmp_path):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    (tmp_path / "reach.cpp").write_text(REACH)
+    exe = tmp_path / "reach"
+    subprocess.run([cxx, "-std=c++17", "-O1", "-I", CSRC, str(tmp_path / "reach.cpp"), "-o",
+                    str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
