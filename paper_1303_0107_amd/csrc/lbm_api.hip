@@ -574,15 +574,10 @@ size_t resident_tiles(const lbm_handle *h, int variant) {
 
 // Region shape of a new lattice (until one is set or tuned).
 int default_shape(lbm_handle *h) {
-    const int n = tb_variant_count(h->precision);
-    std::vector<TbVariant> shapes(n);
-    std::vector<size_t> resident(n);
-    for (int v = 0; v < n; ++v) {
-        shapes[v] = tb_shape(h->precision, v);
-        resident[v] = resident_tiles(h, v);
-    }
-    return start_shape(shapes, resident, (int)h->esize(), h->flags != 0, h->n_nonsolid,
-                       h->host_types.data(), h->nx, h->ny);
+    std::vector<TbVariant> shapes(tb_variant_count(h->precision));
+    for (size_t v = 0; v < shapes.size(); ++v) shapes[v] = tb_shape(h->precision, (int)v);
+    return start_shape(shapes, h->cus, (int)h->esize(), h->flags != 0, h->host_types.data(), h->nx,
+                       h->ny);
 }
 
 // After an exchange step: the autotuned shape while its tiles all run in one

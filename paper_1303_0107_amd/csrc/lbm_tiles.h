@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <cstring>
 #include <utility>
 #include <vector>
 
@@ -18,6 +19,19 @@ enum TbKind : int { kTbDense = 0, kTbCompact = 1, kTbInPlace = 2 };
 struct TbVariant {
     int rows, halo, kind;
 };
+
+// Non-solid cells (types 1 to 3) among n, eight at a time.
+inline int cells_in(const uint8_t *p, int n) {
+    constexpr uint64_t kOnes = 0x0101010101010101u;
+    int c = 0;
+    for (; n >= 8; p += 8, n -= 8) {
+        uint64_t w;
+        std::memcpy(&w, p, 8);
+        c += (int)((((w | w >> 1) & kOnes) * kOnes) >> 56);
+    }
+    for (; n > 0; ++p, --n) c += *p != 0;
+    return c;
+}
 
 // Non-solid cell counts per tile of a tw x th tiling and the tiles that hold
 // one, row-major, packed (tile row << 16 | tile column).
@@ -51,12 +65,8 @@ struct Tilings {
         for (int y = 0; y < ny; ++y) {
             const uint8_t *row = types + (size_t)y * nx;
             int32_t *c = t.count.data() + (size_t)(y / th) * t.ntx;
-            for (int tx = 0; tx < t.ntx; ++tx) {
-                int n = 0;
-                const int x1 = std::min(nx, (tx + 1) * tw);
-                for (int x = tx * tw; x < x1; ++x) n += row[x] != 0;
-                c[tx] += n;
-            }
+            for (int tx = 0; tx < t.ntx; ++tx)
+                c[tx] += cells_in(row + tx * tw, std::min(tw, nx - tx * tw));
         }
         t.relist();
         kept.push_back(std::move(t));
@@ -83,12 +93,8 @@ inline bool tiles_within(const uint8_t *types, int nx, int ny, int tw, int th, s
         std::fill(any.begin(), any.end(), 0);
         for (int y = ty * th; y < std::min(ny, (ty + 1) * th); ++y) {
             const uint8_t *row = types + (size_t)y * nx;
-            for (int tx = 0; tx < ntx; ++tx) {
-                uint8_t v = 0;
-                const int x1 = std::min(nx, (tx + 1) * tw);
-                for (int x = tx * tw; x < x1; ++x) v |= row[x];
-                any[tx] |= v;
-            }
+            for (int tx = 0; tx < ntx; ++tx)
+                if (!any[tx]) any[tx] = cells_in(row + tx * tw, std::min(tw, nx - tx * tw)) > 0;
         }
         for (int tx = 0; tx < ntx; ++tx) n += any[tx] != 0;
         if (n > limit) return false;
@@ -141,39 +147,101 @@ int fitted_shape(int tuned, const std::vector<double> &ms,
     return tuned;
 }
 
+// The most non-solid cells, and the most rows with one, in any region of a
+// shape (64 columns, `rows` rows).  Stops, with what it has found so far, once
+// a region holds more than `enough` cells; it starts at half the height, where
+// an opening is likely.
+struct RegionFill {
+    int cells = 0, live_rows = 0;
+};
+inline RegionFill densest_region(const uint8_t *types, int nx, int ny, int rows, int halo,
+                                 int enough) {
+    const int iw = 64 - 2 * halo, ih = rows - 2 * halo;
+    const int ntx = (nx + iw - 1) / iw, nty = (ny + ih - 1) / ih;
+    std::vector<uint8_t> cells((size_t)ny * ntx), counted(ny);  // per row and 64 columns
+    RegionFill most;
+    for (int k = 0; k < nty; ++k) {
+        const int ty = (nty / 2 + k) % nty;
+        const int y0 = std::max(0, ty * ih - halo), y1 = std::min(ny, ty * ih - halo + rows);
+        for (int y = y0; y < y1; ++y) {
+            if (counted[y]) continue;
+            counted[y] = 1;
+            const uint8_t *row = types + (size_t)y * nx;
+            for (int tx = 0; tx < ntx; ++tx) {
+                const int x0 = std::max(0, tx * iw - halo);
+                cells[(size_t)y * ntx + tx] =
+                    (uint8_t)cells_in(row + x0, std::min(nx, tx * iw + iw + halo) - x0);
+            }
+        }
+        for (int tx = 0; tx < ntx; ++tx) {
+            RegionFill r;
+            for (int y = y0; y < y1; ++y) {
+                const int c = cells[(size_t)y * ntx + tx];
+                r.cells += c;
+                r.live_rows += c != 0;
+            }
+            most.cells = std::max(most.cells, r.cells);
+            most.live_rows = std::max(most.live_rows, r.live_rows);
+        }
+        if (most.cells > enough) return most;
+    }
+    return most;
+}
+
 // Region shape a new lattice starts with (until one is set or tuned): a rule
-// on the precision, the variants and the tile count, never on a size by
-// itself.  resident: as for fitted_shape.  value_bytes: of a stored
-// population.
-//   float   (32,9) dense while its tiles run in one round of workgroups, since
-//           a launch's fixed cost is then spread over most steps; else, and
-//           with boundary variants, (16,4) dense, of which two workgroups
-//           share a CU.  us per step, compacted (32,8) / (16,4) / (32,9):
-//           256 x 128 distributor 1.43 / 1.24 / 1.21; 773 x 391 1.83 / 1.38 /
-//           1.33; 2200 x 1400 7.05 / 4.51 / 5.47; 1000 x 600 channel 7.23 /
-//           4.41 / 4.84; 360 x 180 half collector 1.91 / 1.51 / 1.75.
-//   16-bit  (16,4) dense: 256 x 128 1.51 / 1.38 / 1.43, 2200 x 1400 7.27 /
-//           4.84 / 6.22.
-//   double  (16,4) dense, but compacted with boundary variants (2.30 against
-//           2.68) and on a few wave rows of cells (128 x 64: 1.74 against
-//           1.96; 773 x 391: 2.33 against 2.23).
-inline int start_shape(const std::vector<TbVariant> &shapes, const std::vector<size_t> &resident,
-                       int value_bytes, bool variants, int64_t nonsolid, const uint8_t *types,
-                       int nx, int ny) {
+// on the storage, the variants, the tiles and what the densest region holds,
+// never on a size by itself.  cus: compute units; a 32-row region, and an FP64
+// one, takes a whole CU.  value_bytes: of a stored population.
+//   What a launch does besides its steps (5 us) is spread over nine of them by
+//   (32,9) and over four by (16,4), but a wave of a 32-row region advances two
+//   rows a step, and rows without a cell cost nothing.  us per step, checks
+//   every 100 steps included, compacted (32,8) / (16,4) / (32,9):
+//   float   (32,9) while its tiles run at once, else (16,4): 256 x 128
+//           distributor 1.57 / 1.52 / 1.38; 1200 x 300 2.01 / 1.62 / 1.51; 130
+//           x 60 channel 2.00 / 1.55 / 1.61; lines of 4 rows in 600 x 600
+//           1.27 / 1.42 / 1.04.
+//   16-bit  the conversions make the second row dearer: (32,9) while its tiles
+//           run at once and either no region has more live rows than waves
+//           (FP16: lines of 4 rows 1.39 / 1.52 / 1.17, 100 x 16 channel 1.69 /
+//           1.57 / 1.41, but 40 x 20, 18 rows, 1.60 / 1.63 / 1.63; 256 x 128
+//           distributor, 32 rows, 1.68 / 1.58 / 1.61) or those of (16,4) do
+//           not (1024 x 512: 2.02 / 1.97 / 1.67).
+//   16-bit, and any offset form with boundary variants: compacted while no
+//           region holds over 640 cells, ten waves' worth (FP16 / BF16 against
+//           (16,4): 64 x 48, 399 cells, 0.92 / 0.94; 144 x 90, 625, 0.99 /
+//           0.97; 160 x 80, 670, 1.03 / 1.03; 160 x 100, 792, 1.08 / 1.12; FP32
+//           128 x 64 collector, 440, 0.96); else (16,4).
+//   double  a compacted list packs a region's cells into few waves, a dense
+//           row takes one each: compacted while the tiles run at once and the
+//           densest region has at most 40 cells per live row (compacted against dense: 64 x 48
+//           distributor, 18, 0.91; 24 x 12 channel, 24, 0.90; 112 x 64, 31,
+//           0.98; 160 x 80, 34, 0.99; 40 x 20 channel, 40, 0.97; 144 x 90, 41,
+//           1.09; 256 x 128, 45, 1.08; lines of 4 rows, 64, 1.10), and with
+//           boundary variants (360 x 180 half collector 0.90).
+inline int start_shape(const std::vector<TbVariant> &shapes, int cus, int value_bytes,
+                       bool variants, const uint8_t *types, int nx, int ny) {
     auto find = [&](int rows, int halo, int kind) {
         for (size_t v = 0; v < shapes.size(); ++v)
             if (shapes[v].rows == rows && shapes[v].halo == halo && shapes[v].kind == kind)
                 return (int)v;
         return 0;
     };
-    if (value_bytes == 8)
-        return find(16, 4, variants || nonsolid < 40 * 64 ? kTbCompact : kTbDense);
-    if (value_bytes == 4 && !variants) {
-        const int v = find(32, 9, kTbDense);
-        if (tiles_within(types, nx, ny, 64 - 2 * shapes[v].halo,
-                         shapes[v].rows - 2 * shapes[v].halo, resident[v]))
-            return v;
+    auto one_each = [&](int rows, int halo) {
+        return tiles_within(types, nx, ny, 64 - 2 * halo, rows - 2 * halo, cus);
+    };
+    if (value_bytes == 8) {
+        if (variants) return find(16, 4, kTbCompact);
+        if (!one_each(16, 4)) return find(16, 4, kTbDense);
+        const RegionFill r = densest_region(types, nx, ny, 16, 4, 40 * 16);
+        return find(16, 4, r.cells <= 40 * r.live_rows ? kTbCompact : kTbDense);
     }
+    if (!variants && one_each(32, 9) &&
+        (value_bytes == 4 || !one_each(16, 4) ||
+         densest_region(types, nx, ny, 32, 9, 64 * 16).live_rows <= 16))
+        return find(32, 9, kTbDense);
+    if ((value_bytes == 2 || variants) && one_each(32, 8) &&
+        densest_region(types, nx, ny, 32, 8, 640).cells <= 640)
+        return find(32, 8, kTbCompact);
     return find(16, 4, kTbDense);
 }
 
