@@ -710,29 +710,13 @@ int default_march(const lbm_handle *h) {
     return on ? march_steps(h) : 0;
 }
 
-// Segments of a marching launch: the shortest (at least four rows) for which
-// all workgroups run at once with `fill` waves on each SIMD.  Fewer waves do
-// not hide the latency of their own instructions, more only lengthen the
-// launch by the rows that each segment advances beyond its ends.  us per
-// step with 1, 2 and 3: 4096 x 2048 FP32, 7 steps, 33.6, 29.6, 32.3; 2000 x
-// 1000 FP32, 6 steps, 10.5 (7 steps), 7.9, 8.5; 2000 x 1000 FP16, 4 steps,
-// 9.3 with 3 and 9.8 with 4.
+// Waves per SIMD of a marching launch.  us per step with 1, 2 and 3: 4096 x
+// 2048 FP32, 7 steps, 33.6, 29.6, 32.3; 2000 x 1000 FP32, 6 steps, 10.5 (7
+// steps), 7.9, 8.5; 2000 x 1000 FP16, 4 steps, 9.3 with 3 and 9.8 with 4.
 MarchPlan march_plan(const lbm_handle *h, int steps) {
     const int fill = steps <= 4 && h->precision != LBM_F64 ? 3 : 2;
-    const int target = fill * h->cus * (kMarchThreads / 64);
-    const int iw = 64 - 2 * steps;
-    MarchPlan p{};
-    p.steps = steps;
-    p.strips = (h->nx + iw - 1) / iw;
-    for (p.rows = std::max(4, (int)((int64_t)h->ny * p.strips / target));; ++p.rows) {
-        p.segs = (h->ny + p.rows - 1) / p.rows;
-        p.edge_rows = (p.rows + 1) / 2;
-        p.edge_segs = (h->ny + p.edge_rows - 1) / p.edge_rows;
-        p.waves = 2 * p.edge_segs + (p.strips - 2) * p.segs;
-        if (p.waves <= target || p.rows >= h->ny) break;
-    }
-    p.blocks = (p.waves + kMarchThreads / 64 - 1) / (kMarchThreads / 64);
-    return p;
+    const bool in_cache = h->f[0].bytes + h->f[1].bytes <= (size_t)256 << 20;
+    return lbm::march_plan(h->nx, h->ny, steps, h->cus, fill, in_cache);
 }
 
 // Steps of the next marching launch when n are left.

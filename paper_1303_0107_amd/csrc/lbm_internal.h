@@ -8,6 +8,7 @@
 
 #include <type_traits>
 
+#include "lbm_march_plan.h"
 #include "lbm_tiles.h"
 
 struct lbm_handle;
@@ -225,15 +226,8 @@ hipError_t launch_tb_batch(const SweepArgs<T> *args, const int32_t *lat, const i
 template <typename T>
 hipError_t launch_step_batch(const SweepArgs<T> *args, const int32_t *lat,
                              const int32_t *blocks, int n_items, bool bc, hipStream_t s);
-// The marching sweep (lbm_march.h): `steps` (1, 2, 4; in float also 6, 7) time steps a launch, one wave per
-// strip of 64 - 2 steps columns and segment of rows.  Interior strips are cut
-// into `segs` segments of `rows` rows, the two edge strips into `edge_segs`
-// of `edge_rows`; `blocks` workgroups of kMarchThreads hold the waves.
-// Lattices of at least two strips without boundary-variant flags.
-constexpr int kMarchThreads = 256;
-struct MarchPlan {
-    int steps, strips, segs, rows, edge_segs, edge_rows, waves, blocks;
-};
+// The marching sweep (lbm_march.h, lbm_march_plan.h) on lattices of at least
+// two strips without boundary-variant flags.
 // Waves per SIMD a marching kernel is compiled for: what its registers (12 a
 // step and about 70, twice as many in double) leave of 512.
 constexpr int march_waves(int steps, size_t arith_bytes, bool check) {

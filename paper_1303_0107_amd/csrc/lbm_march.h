@@ -1,7 +1,7 @@
 // The marching sweep: several time steps of a dense lattice in registers.
 //
-// One wavefront owns a strip of 64 lattice columns (64 - 2S of them its own,
-// S on each side a halo) over a segment of rows, and walks up the rows with
+// One wavefront owns a strip of 64 lattice columns (at most 64 - 2S of them its
+// own, the others a halo) over a segment of rows, and walks up the rows with
 // all S time steps in flight: when row t of the input arrives, step 1 is
 // carried out on row t - 1, step 2 on row t - 2, and so on to step S on row
 // t - S, which is written out.  Step s of a row needs the rows below, at and
@@ -155,7 +155,6 @@ __global__ __launch_bounds__(kMarchThreads, march_waves(S, sizeof(typename Cell:
                                                               SweepArgs<typename Cell::T> a) {
     using T = typename Cell::T;
     using CT = typename Cell::CT;
-    constexpr int IW = 64 - 2 * S;
     const int lane = threadIdx.x & 63;
     if (__builtin_amdgcn_readfirstlane(stop[lane])) return;  // the run has ended (all lanes alike)
 
@@ -168,10 +167,10 @@ __global__ __launch_bounds__(kMarchThreads, march_waves(S, sizeof(typename Cell:
     const MarchWave m = march_wave(plan, w, a.ny);
     const int y0 = m.y0, y1 = m.y1;
 
-    const int gx = m.strip * IW - S + lane;
+    const int gx = m.strip * plan.width - S + lane;
     const bool col_in = gx >= 0 && gx < a.nx;
     const uint32_t col = col_in ? (uint32_t)gx : 0u;
-    const bool own = lane >= S && lane < 64 - S && col_in;
+    const bool own = lane >= S && lane < S + plan.width && col_in;
     const int lo = max(0, y0 - S), hi = min(a.ny, y1 + S);  // rows to read
 
     // Slots of step s - 1's rows as step s sees them in phase p: row y + 1 in
