@@ -671,50 +671,49 @@ MacroArgs<T> macro_args(lbm_handle *h) {
     return a;
 }
 
-// Lattices of at least this many cells march untuned: below, a segment has too
-// few rows for what it advances beyond its ends.  us per step against the
-// best region shape, all-fluid channels, timed with a shorter float update on
-// both sides (now 2000 steps of 4096 x 2048 take 97 ms against 148 blocked,
-// 2000 x 1000 FP16 28 against 36, read-back included), FP32: 1024 x 512 4.6 against 4.0,
-// 1400 x 700 5.9 against 6.3, 1700 x 850 6.8 against 8.4, 2300 x 2000 15.6
-// against 29.3; FP16: 1400 x 700 6.7 against 6.8, 2300 x 2000 18.6 against
-// 27.6; FP64: 700 x 350 6.1 against 5.3, 1024 x 512 7.7 against 8.2, 1400 x
-// 700 10.5 against 14.9, 2300 x 2000 50 against 62.  The autotuner times both
-// from kMarchTuneCells on.
-constexpr int64_t kMarchCells = 900000, kMarchCells64 = (int64_t)1 << 19,
-                  kMarchTuneCells = (int64_t)1 << 19;
-
 // Whether the marching sweep (lbm_march.h) can run on a lattice: it has no
 // boundary-variant paths and needs two strips.
 bool can_march(const lbm_handle *h) { return h->use_tb && h->flags == 0 && h->nx >= 128; }
 
-// Whether it is considered: it advances solid cells too, the blocked sweep
-// skips tiles without fluid, so only on lattices that are mostly fluid.
+// Whether it is considered: only on lattices that are mostly fluid, since the
+// blocked sweep skips tiles without fluid.
 bool may_march(const lbm_handle *h) {
     return can_march(h) && h->march_env != 0 && 4 * h->n_nonsolid >= 3 * (int64_t)h->N();
 }
 
-// Steps of a marching launch.  In double the registers end at 4; otherwise 6,
-// or 7 on the largest lattices, which HBM bounds (us per step with 4, 6 and 7:
-// 1700 x 850 FP32 8.2, 6.8, 7.0; 2300 x 2000 FP32 24.4, 17.6, 15.6; FP16 20.5,
-// 18.6, 18.9).  Eight spill.
+MarchRule march_rule(const lbm_handle *h) {
+    return lbm::march_rule((int)h->esize(), (int64_t)h->N(), h->n_nonsolid, h->nx);
+}
+
+// Steps of a marching launch.
 int march_steps(const lbm_handle *h) {
     if (h->march_env > 0) return std::min(h->march_env, h->precision == LBM_F64 ? 4 : 7);
-    return h->precision == LBM_F64 ? 4 : h->N() < (size_t)4 << 20 ? 6 : 7;
+    return march_rule(h).steps;
+}
+
+// Cells of the tiles that the blocked sweep would advance (current tile list).
+int64_t tiled_cells(const lbm_handle *h) {
+    return std::min<int64_t>((int64_t)h->N(),
+                             (int64_t)h->n_tiles * tile_width(h->precision, h->tb_variant) *
+                                 tile_height(h->precision, h->tb_variant));
 }
 
 // Steps per launch before (or without) the autotuner; 0: the blocked sweep.
 int default_march(const lbm_handle *h) {
-    const int64_t from = h->precision == LBM_F64 ? kMarchCells64 : kMarchCells;
-    const bool on = h->march_env > 0 ? can_march(h) : may_march(h) && (int64_t)h->N() >= from;
+    const bool on = h->march_env > 0 ? can_march(h)
+                                     : may_march(h) && tiled_cells(h) >= march_rule(h).from;
     return on ? march_steps(h) : 0;
 }
 
-// Waves per SIMD of a marching launch.  us per step with 1, 2 and 3: 4096 x
-// 2048 FP32, 7 steps, 33.6, 29.6, 32.3; 2000 x 1000 FP32, 6 steps, 10.5 (7
-// steps), 7.9, 8.5; 2000 x 1000 FP16, 4 steps, 9.3 with 3 and 9.8 with 4.
+// Whether the autotuner times the marching sweep too: from three quarters of
+// the size at which it is the faster one untuned.
+bool tunes_march(const lbm_handle *h) {
+    return may_march(h) && 4 * tiled_cells(h) >= 3 * march_rule(h).from;
+}
+
 MarchPlan march_plan(const lbm_handle *h, int steps) {
-    const int fill = steps <= 4 && h->precision != LBM_F64 ? 3 : 2;
+    const int fill = march_fill((int)h->esize(), steps,
+                                clear((int64_t)h->N(), h->n_nonsolid, h->nx));
     const bool in_cache = h->f[0].bytes + h->f[1].bytes <= (size_t)256 << 20;
     return lbm::march_plan(h->nx, h->ny, steps, h->cus, fill, in_cache);
 }
@@ -2200,7 +2199,7 @@ int lbm_autotune(lbm_handle *h, int32_t trial_steps, int32_t *best, double *ms,
         // the marching sweep, where it is considered, takes the place of the
         // best shape when it is faster
         int march = 0;
-        if (may_march(h) && (int64_t)h->N() >= kMarchTuneCells) {
+        if (tunes_march(h)) {
             h->march = march_steps(h);
             const double t = with_storage(h->precision, [&](auto x) {
                 return time_handle_steps<decltype(x)>(h, trial_steps);

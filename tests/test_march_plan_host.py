@@ -60,3 +60,49 @@ def test_strips_cover_the_lattice_and_only_edge_strips_see_a_boundary(tmp_path, 
                     str(tmp_path / "plan.cpp"), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe), str(steps)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+RULE = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "lbm_march_plan.h"
+// argv: value_bytes cells nonsolid nx; prints from, steps, and the waves per
+// SIMD of launches of that many steps and of two
+int main(int, char **argv) {
+    const int bytes = std::atoi(argv[1]), nx = std::atoi(argv[4]);
+    const long long cells = std::atoll(argv[2]), nonsolid = std::atoll(argv[3]);
+    const lbm::MarchRule r = lbm::march_rule(bytes, cells, nonsolid, nx);
+    const bool c = lbm::clear(cells, nonsolid, nx);
+    std::printf("%lld %d %d %d\n", (long long)r.from, r.steps, lbm::march_fill(bytes, r.steps, c),
+                lbm::march_fill(bytes, 2, c));
+    return 0;
+}
+"""
+
+
+# channels, channels with solid cells up to and past one in a thousand, and the
+# step count of the largest
+@pytest.mark.parametrize("value_bytes,nx,ny,solid,want", [
+    (8, 1024, 512, 0, [500000, 4, 2, 2]),
+    (8, 4096, 2048, 80000, [500000, 4, 2, 2]),
+    (4, 1500, 760, 0, [1100000, 6, 2, 2]),
+    (4, 1500, 760, 1140, [1100000, 6, 2, 2]),
+    (4, 1500, 760, 1141, [2400000, 6, 3, 2]),
+    (4, 2048, 2047, 0, [1100000, 6, 2, 2]),
+    (4, 2048, 2048, 0, [1100000, 7, 2, 2]),
+    (4, 2048, 2048, 90000, [2400000, 7, 2, 2]),
+    (2, 1500, 760, 0, [1100000, 4, 3, 3]),
+    (2, 4096, 2048, 90000, [2400000, 4, 3, 3]),
+])
+def test_which_lattices_march(tmp_path, value_bytes, nx, ny, solid, want):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    (tmp_path / "rule.cpp").write_text(RULE)
+    exe = tmp_path / "rule"
+    subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Werror", "-I", CSRC,
+                    str(tmp_path / "rule.cpp"), "-o", str(exe)], check=True)
+    cells = nx * ny
+    out = subprocess.run([str(exe), str(value_bytes), str(cells), str(cells - 2 * nx - solid),
+                          str(nx)], check=True, capture_output=True, text=True).stdout
+    assert [int(v) for v in out.split()] == want
