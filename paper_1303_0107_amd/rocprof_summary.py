@@ -17,7 +17,11 @@ import re
 import subprocess
 
 
-SHORT = [("lbm::OffsetCell<float, float, float>", "F32Cell"),
+SHORT = [("lbm::OffsetCell<float, float>", "F32Cell"),
+         ("lbm::OffsetCell<_Float16, float>", "H16Cell"),
+         ("lbm::OffsetCell<__hip_bfloat16, float>", "BF16Cell"),
+         # traces from before the cells had two parameters
+         ("lbm::OffsetCell<float, float, float>", "F32Cell"),
          ("lbm::OffsetCell<float, double, double>", "F32Cell(double arithmetic)"),
          ("lbm::OffsetCell<_Float16, float, float>", "H16Cell"),
          ("lbm::OffsetCell<__hip_bfloat16, float, float>", "BF16Cell"),
@@ -25,10 +29,10 @@ SHORT = [("lbm::OffsetCell<float, float, float>", "F32Cell"),
          ("lbm::sweep::", ""), ("lbm::", "")]
 
 
-# Mangled blocked-sweep names that c++filt leaves alone (it does not know the
-# _Float16 mangling): tb_kernel / tb_batch_kernel of an offset cell.
-_TB = re.compile(r"_ZN3lbm5sweep(\d+)(tb_kernel|tb_batch_kernel)INS_10OffsetCellI"
-                 r"(DF16_|14__hip_bfloat16|f)ffEE((?:L[ib]\d+E)+)")
+# Mangled sweep names that c++filt leaves alone (it does not know the _Float16
+# mangling): kernels of an offset cell.
+_TB = re.compile(r"_ZN3lbm(?:5sweep)?(\d+)([a-z_]+?_kernel)INS_10OffsetCellI"
+                 r"(DF16_|14__hip_bfloat16|f)ff?EE((?:L[ib]\d+E)+)")
 _CELL = {"DF16_": "H16Cell", "14__hip_bfloat16": "BF16Cell", "f": "F32Cell"}
 
 

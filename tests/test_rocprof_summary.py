@@ -47,3 +47,15 @@ def test_mangled_half_precision_sweep_names():
     name = ("_ZN3lbm5sweep9tb_kernelINS_10OffsetCellIDF16_ffEELi32ELi9ELi1024ELi0ELb0ELb1EEEv"
             "NS_9SweepArgsINT_1TEEEPKii")
     assert R.short(name) == "tb_kernel<H16Cell, 32, 9, 1024, 0, false, true>"
+
+
+def test_names_of_two_parameter_cells():
+    assert R.short("void lbm::sweep::march_kernel<lbm::OffsetCell<float, float>, 7, true>(int)"
+                   ) == "march_kernel<F32Cell, 7, true>"
+    assert R.short("_ZN3lbm5sweep12march_kernelINS_10OffsetCellIDF16_fEELi4ELb1EEEvPKiNS_9MarchPlan"
+                   "ENS_9SweepArgsINT_1TEEE") == "march_kernel<H16Cell, 4, true>"
+    assert R.short("_ZN3lbm5sweep9tb_kernelINS_10OffsetCellIDF16_fEELi16ELi4ELi1024ELi0ELb0ELb0ELb0"
+                   "EEEvPKiS5_iNS_9SweepArgsINT_1TEEE") == \
+        "tb_kernel<H16Cell, 16, 4, 1024, 0, false, false, false>"
+    assert R.short("_ZN3lbm15boundary_kernelINS_10OffsetCellIDF16_fEELb0EEEvNS_9SweepArgs"
+                   ) == "boundary_kernel<H16Cell, false>"
