@@ -472,10 +472,47 @@ MEASURED_VALU_PER_LAUNCH = {
     ("batch-256-candidates", "f32", 6, 0): 43.54e6,
 }
 VALU_PEAK_WAVE_INSTR_PER_S = 256 * 4 * 2.4e9 / 4
+# What the SIMDs issue at best, measured: 2.3 cycles an FP32 instruction, 4.6 an
+# FP64 one (two or more waves on the SIMD).
+VALU_MEASURED_CYCLES = {"f32": 2.3, "f64": 4.6}
 
 
-def hbm_and_limiter(roof: dict, traffic, valu, avg_ms: float) -> None:
-    """Add the measured HBM rate and the ALU-issue bound to a roofline dict."""
+def march_launches(n: int, steps: int) -> int:
+    """Launches that n time steps take in the marching sweep of `steps` steps a
+    launch: the largest compiled step counts first."""
+    count = 0
+    for s in (7, 6, 4, 2, 1):
+        if s <= steps:
+            count, n = count + n // s, n % s
+    return count
+
+
+def marching_steps(lat, halo: int) -> int:
+    """Steps per launch of the marching sweep if handle `lat` uses it, 0 if it
+    runs the blocked sweep (`halo` steps per launch), told by the launches of
+    99 time steps, which differ between all of them.  Advances the state."""
+    lat.profile_sweeps(True)
+    lat.run(99, 0.0, 99)
+    _, launches, _ = lat.profile_sweeps(False)
+    if launches in (-(-99 // halo), 99):
+        return 0
+    for steps in (7, 6, 4, 2):
+        if launches == march_launches(99, steps):
+            return steps
+    raise RuntimeError(f"99 steps in {launches} launches: no sweep known takes as many")
+
+
+def kernel_label(storage: str, march: int, shape: int, rows: int, halo: int,
+                 steps_per_launch: float) -> str:
+    if march:
+        return f"march_kernel ({storage} storage, {march} steps per launch)"
+    name = "tb_kernel" if steps_per_launch > 1.0 else "step_kernel"
+    return f"{name} ({storage} storage, shape {shape}: {rows}x64 region, {halo} steps per launch)"
+
+
+def hbm_and_limiter(roof: dict, traffic, valu, avg_ms: float, arith: str = "f32") -> None:
+    """Add the measured HBM rate and the vector-issue rate to a roofline dict:
+    the share of the nominal rate (frac) and of the measured one."""
     roof["effective"] = "algorithmic bytes of every step a launch advances over the launch " \
                         "time (with temporal blocking, above what HBM carries)"
     if traffic:
@@ -491,6 +528,8 @@ def hbm_and_limiter(roof: dict, traffic, valu, avg_ms: float) -> None:
                            "peak": round(VALU_PEAK_WAVE_INSTR_PER_S / 1e9, 1),
                            "unit": "G wave-instructions/s",
                            "frac": round(rate / VALU_PEAK_WAVE_INSTR_PER_S, 4),
+                           "frac_of_measured_rate": round(
+                               rate * VALU_MEASURED_CYCLES[arith] / (256 * 4 * 2.4e9), 4),
                            "valu_per_launch": valu}
     else:
         roof["limiter"] = None
@@ -555,6 +594,8 @@ def optimise_leg(args, w, prec_name: str, copy_gbs: float):
     wall = time.perf_counter() - t0
     timed_steps, launches, sweep_ms = lat.profile_sweeps(False)
     in_use = lbm.lbm_get_tb_variant(lat.h)
+    in_use_rows, in_use_halo, _, _ = lbm.lbm_tb_variant_info(prec, in_use if in_use >= 0 else shape)
+    march = marching_steps(lat, in_use_halo)
 
     mlups = N * sweeps / wall / 1e6
     bytes_per_step = 18 * s_bytes * nns + N
@@ -564,16 +605,16 @@ def optimise_leg(args, w, prec_name: str, copy_gbs: float):
     achieved = bytes_per_launch / (avg_ms * 1e-3) / 1e9
     n, res, flow, st, r = last
     spread = float((flow.max() - flow.min()) / flow.mean()) if len(flow) else 0.0
-    kernel = "tb_kernel" if steps_per_launch > 1.0 else "step_kernel"
-    full = MEASURED_TRAFFIC_PER_FULL_LAUNCH.get((w.name, prec_name, in_use))
-    per_interval = -(-k // halo)  # launches per check interval
+    measured = (w.name, prec_name, in_use) if not march else None
+    full = MEASURED_TRAFFIC_PER_FULL_LAUNCH.get(measured)
+    per_interval = -(-k // in_use_halo)  # launches per check interval
     traffic = round(full + 32 * nns / per_interval) if full else None
-    valu = MEASURED_VALU_PER_FULL_LAUNCH.get((w.name, prec_name, in_use))
+    valu = MEASURED_VALU_PER_FULL_LAUNCH.get(measured)
     roof = {
         "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
         "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-        "kernel": kernel + f" ({prec_name} storage, shape {in_use}: {rows}x64 region, "
-                           f"{halo} steps per launch)",
+        "kernel": kernel_label(prec_name, march, in_use, in_use_rows, in_use_halo,
+                               steps_per_launch),
         "bytes_per_step": bytes_per_step, "steps_per_launch": round(steps_per_launch, 3),
         "bytes_per_launch": round(bytes_per_launch), "launches": launches,
         "launch_timing": "HIP events on the handle's stream around the launches of every "
@@ -582,7 +623,7 @@ def optimise_leg(args, w, prec_name: str, copy_gbs: float):
         "copy_ceiling_GBs": round(copy_gbs, 1),
         "frac_of_copy_ceiling": round(achieved / copy_gbs, 4),
     }
-    hbm_and_limiter(roof, traffic, valu, avg_ms)
+    hbm_and_limiter(roof, traffic, valu, avg_ms, arith)
     out = {
         "metric": METRIC,
         "value": round(mlups, 2),
@@ -607,7 +648,7 @@ def optimise_leg(args, w, prec_name: str, copy_gbs: float):
             "last_spread": spread, "last_residual": res,
             "last_flux_period_two": st.flow_p2,
             "tuned_shape": {"index": shape, "rows": rows, "halo": halo, "tile": [tw, th]},
-            "shape_in_use": in_use,
+            "shape_in_use": in_use if not march else None,
             "tune_us_per_step": [round(x * 1e3, 3) for x in tune_ms],
             "exchange_ms_median": round(float(np.median(ex_ms)), 3),
             "stats_ms_median": round(float(np.median(stats_ms)), 3),
@@ -644,25 +685,27 @@ def sweep_leg(args, w, prec_name: str, steps: int, copy_gbs: float):
     wall = time.perf_counter() - t0
     timed_steps, launches, sweep_ms = lat.profile_sweeps(False)
     in_use = lbm.lbm_get_tb_variant(lat.h)
+    march = marching_steps(lat, halo)
     lat.close()
     bytes_per_step = 18 * s_bytes * nns + N
     avg_ms = sweep_ms / max(launches, 1)
     spl = timed_steps / max(launches, 1)
     achieved = bytes_per_step * spl / (avg_ms * 1e-3) / 1e9
-    full = MEASURED_TRAFFIC_PER_FULL_LAUNCH.get((w.name, prec_name, in_use))
+    measured = (w.name, prec_name, in_use) if not march else None
+    full = MEASURED_TRAFFIC_PER_FULL_LAUNCH.get(measured)
     per_interval = -(-100 // halo)
     traffic = round(full + 32 * nns / per_interval) if full else None
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
             "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-            "kernel": f"tb_kernel ({prec_name} storage, shape {in_use}: {rows}x64 region, "
-                      f"{halo} steps per launch)",
+            "kernel": kernel_label(prec_name, march, in_use, rows, halo, spl),
             "bytes_per_step": bytes_per_step, "avg_launch_us": round(avg_ms * 1e3, 3),
             "steps_per_launch": round(spl, 3),
             "frac_of_copy_ceiling": round(achieved / copy_gbs, 4)}
-    hbm_and_limiter(roof, traffic, MEASURED_VALU_PER_FULL_LAUNCH.get((w.name, prec_name, in_use)),
-                    avg_ms)
-    print(f"# {w.name}: {steps} steps in {wall * 1e3:.1f} ms, shape {in_use}", file=sys.stderr,
-          flush=True)
+    hbm_and_limiter(roof, traffic, MEASURED_VALU_PER_FULL_LAUNCH.get(measured), avg_ms,
+                    prec_name if prec_name == "f64" else "f32")
+    print(f"# {w.name}: {steps} steps in {wall * 1e3:.1f} ms, "
+          + (f"marching {march} steps a launch" if march else f"shape {in_use}"),
+          file=sys.stderr, flush=True)
     return {"workload": w.name, "storage": prec_name, "steps": steps,
             "value": round(N * steps / wall / 1e6, 2), "unit": "MLUPS",
             "mflups": round(nns * steps / wall / 1e6, 2),
