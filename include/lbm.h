@@ -200,8 +200,8 @@ int lbm_run_to_steady(lbm_handle *h, int64_t max_steps, double tol,
  * (a few percent of the outlet flux on the distributors), which the residual
  * of lbm_run_to_steady does not see; the two-step mean cancels it.  flow_in
  * and dp are means in the same way, theta, dg and flow_ave are taken on the
- * mean fluxes, mass is the current state's.  The later state is computed in
- * the handle's second population buffer; the current state is not changed.
+ * mean fluxes, mass is the current state's.  Of the later state only the
+ * boundary cells are computed, inside the sums; no population is written.
  * All sums are double precision and run in a fixed order, so repeated calls
  * give identical bits.
  * Errors: LBM_EINVAL if flow_cap < n_outlets (s->n_outlets is still set), or a
@@ -333,8 +333,10 @@ int lbm_profile_sweeps(lbm_handle *h, int32_t enable, int64_t *steps,
  * 64 x rows cells into LDS and advances its inner tile of (64 - 2 halo) x
  * (rows - 2 halo) cells by up to `halo` time steps of Sec. 2.1 (the ring of
  * width halo around the tile is recomputed by its neighbours).  The shape
- * changes only the speed: every shape gives the same bits as one sweep per
- * step.
+ * changes only the speed: every shape gives the same populations, bit for
+ * bit, as one sweep per step.  (The sums of the residual are taken per tile
+ * first, so its last bits may differ from shape to shape, and from those of
+ * the marching sweep.)
  *
  * lbm_tb_variant_count: number of shapes compiled for a precision (0 for an
  * unknown precision).  lbm_tb_variant_info: shape `variant` of `precision`;
@@ -374,11 +376,13 @@ int lbm_get_tb_variant(lbm_handle *h, int32_t *variant);
 
 /*
  * Autotuner: time every compiled shape on `trial_steps` (>= 1) real time
- * steps of this lattice, keep the fastest, and leave the state, the step
+ * steps of this lattice, and on a large one that is mostly fluid the marching
+ * sweep too, keep the fastest, and leave the state, the step
  * counter and the residual exactly as they were (both population buffers
  * are saved and restored, so the call needs their size again in scratch
  * memory while it runs).
- *   best  receives the chosen shape (may be NULL).
+ *   best  receives the chosen shape, the fastest of them also where the
+ *         marching sweep is faster still and is kept (may be NULL).
  *   ms    receives the mean time per step of each shape (ms_cap entries;
  *         may be NULL when ms_cap is 0).
  * The timings are kept: if a later lbm_shape_update leaves the chosen
