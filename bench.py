@@ -20,9 +20,11 @@ roofline: the sweep kernel.  Algorithmic bytes per time step
          (the populations cross HBM once per launch, not once per step), so
          this is an effective bandwidth; the measured HBM bytes per launch
          (rocprofv3 counters) over the same launch time are reported beside
-         it, and so is the kernel's actual limiter, the vector ALU issue rate
-         (measured VALU instructions per launch over the launch time, against
-         the chip's non-packed rate).
+         it, and so is the vector ALU issue rate, under "limiter" (measured
+         VALU instructions per launch over the launch time, against the
+         chip's nominal non-packed rate and against the rate its SIMDs reach;
+         on small lattices the latency of a step's chain bounds the launch
+         before either).
 Default legs (--legs): the headline optimisation loop; the all-fluid
 1024x512 channel (sweeps only: the workload the HBM-roofline target is set
 on); a short serving run (Poisson arrivals, p50/p99 latency).
@@ -57,23 +59,23 @@ MEASURED_TRAFFIC_PER_FULL_LAUNCH = {
     # profiles/sweep_tb_float_distributor-1024x512.txt: shape 5 (32x64 dense
     # regions, 9 steps per launch, 236 active tiles), shape 1 (32x64 dense, 8
     # steps per launch, 234 tiles), shape 0 (32x64 compacted)
-    ("distributor-1024x512-L3", "f32", 5): 8.486e6,
-    ("distributor-1024x512-L3", "f32", 1): 8.403e6,
-    ("distributor-1024x512-L3", "f32", 0): 8.474e6,
+    ("distributor-1024x512-L3", "f32", 5): 8.492e6,
+    ("distributor-1024x512-L3", "f32", 1): 8.419e6,
+    ("distributor-1024x512-L3", "f32", 0): 8.477e6,
     # profiles/sweep_tb_double_distributor-1024x512.txt: shape 3 (32x64 in
     # place, 8 steps per launch), shape 0 (16x64 compacted, 4 steps per
     # launch), shape 1 (16x64 dense)
-    ("distributor-1024x512-L3", "f64", 3): 18.718e6,
-    ("distributor-1024x512-L3", "f64", 0): 13.163e6,
-    ("distributor-1024x512-L3", "f64", 1): 13.133e6,
+    ("distributor-1024x512-L3", "f64", 3): 18.699e6,
+    ("distributor-1024x512-L3", "f64", 0): 13.150e6,
+    ("distributor-1024x512-L3", "f64", 1): 13.135e6,
     # profiles/sweep_tb_float_channel-1024x512.txt: shape 4 (16x64 dense, 4
     # steps per launch), shape 3 (16x64 compacted), shapes 1 and 0 (32x64
     # dense and compacted, 8 steps per launch), shape 5 (32x64 dense, 9 steps)
-    ("channel-1024x512", "f32", 4): 41.012e6,
-    ("channel-1024x512", "f32", 3): 41.030e6,
-    ("channel-1024x512", "f32", 1): 43.170e6,
-    ("channel-1024x512", "f32", 0): 43.250e6,
-    ("channel-1024x512", "f32", 5): 44.016e6,
+    ("channel-1024x512", "f32", 4): 41.016e6,
+    ("channel-1024x512", "f32", 3): 41.031e6,
+    ("channel-1024x512", "f32", 1): 43.218e6,
+    ("channel-1024x512", "f32", 0): 43.252e6,
+    ("channel-1024x512", "f32", 5): 44.088e6,
 }
 # The same for the batched kernel, per launch, keyed by (workload, storage,
 # shape, order).
@@ -82,20 +84,20 @@ MEASURED_TRAFFIC_PER_LAUNCH = {
     # blocking (0: 32x64 compacted, 1: 32x64 dense, 2: 32x64 compacted with
     # 4 steps per launch, 3: 16x64 compacted, 4: 16x64 dense, 5: 32x64 dense
     # with 9 steps per launch), 6 = one step per launch
-    ("batch-256-candidates", "f32", 4, 1): 700.888e6,
-    ("batch-256-candidates", "f32", 4, 0): 1366.060e6,
-    ("batch-256-candidates", "f32", 3, 1): 700.887e6,
-    ("batch-256-candidates", "f32", 3, 0): 1366.061e6,
-    ("batch-256-candidates", "f32", 2, 1): 708.363e6,
-    ("batch-256-candidates", "f32", 2, 0): 1090.876e6,
-    ("batch-256-candidates", "f32", 1, 1): 709.157e6,
-    ("batch-256-candidates", "f32", 1, 0): 1556.352e6,
-    ("batch-256-candidates", "f32", 0, 1): 709.222e6,
-    ("batch-256-candidates", "f32", 0, 0): 1556.446e6,
-    ("batch-256-candidates", "f32", 5, 1): 708.557e6,
-    ("batch-256-candidates", "f32", 5, 0): 1637.074e6,
-    ("batch-256-candidates", "f32", 6, 1): 684.537e6,
-    ("batch-256-candidates", "f32", 6, 0): 775.521e6,
+    ("batch-256-candidates", "f32", 4, 1): 700.910e6,
+    ("batch-256-candidates", "f32", 4, 0): 1366.224e6,
+    ("batch-256-candidates", "f32", 3, 1): 700.919e6,
+    ("batch-256-candidates", "f32", 3, 0): 1366.241e6,
+    ("batch-256-candidates", "f32", 2, 1): 708.388e6,
+    ("batch-256-candidates", "f32", 2, 0): 1091.031e6,
+    ("batch-256-candidates", "f32", 1, 1): 709.184e6,
+    ("batch-256-candidates", "f32", 1, 0): 1556.514e6,
+    ("batch-256-candidates", "f32", 0, 1): 709.252e6,
+    ("batch-256-candidates", "f32", 0, 0): 1556.644e6,
+    ("batch-256-candidates", "f32", 5, 1): 708.589e6,
+    ("batch-256-candidates", "f32", 5, 0): 1637.252e6,
+    ("batch-256-candidates", "f32", 6, 1): 684.556e6,
+    ("batch-256-candidates", "f32", 6, 0): 775.684e6,
 }
 
 
@@ -436,40 +438,41 @@ def bench_serve(args) -> int:
 
 
 # Vector ALU instructions (wave instructions, rocprofv3 SQ_INSTS_VALU) of one
-# full launch of the blocked sweep, keyed like the traffic table.  (Lattices
-# that march, such as the 4096x2048 channel, have no entry.)  The limiter's peak
-# is the nominal rate of 64 lanes on 16-wide SIMDs, 4 cycles an instruction: 256
-# CUs x 4 SIMDs x 2.4 GHz / 4 = 614.4 G wave instructions per second.  Measured,
-# an FP32 instruction takes a SIMD 2.3-2.8 cycles with two or more waves on it
-# (FP64 4.6-5.3), so for FP32 the share of what the chip can issue is about
-# half of the fraction reported.
+# full launch of the blocked sweep, keyed like the traffic table, from the same
+# profiles.  (Lattices that march, such as the 4096x2048 channel, have no
+# entry; profiles/sweep_march_float_channel-4096x2048.txt has their counters.)
+# The limiter's peak is the nominal rate of 64 lanes on 16-wide SIMDs, 4 cycles
+# an instruction: 256 CUs x 4 SIMDs x 2.4 GHz / 4 = 614.4 G wave instructions
+# per second.  Measured, an FP32 instruction takes a SIMD 2.3-2.8 cycles with
+# two or more waves on it (FP64 4.6-5.3), so for FP32 the share of what the chip
+# can issue (frac_of_measured_rate) is about half of the nominal fraction.
 MEASURED_VALU_PER_FULL_LAUNCH = {
-    ("distributor-1024x512-L3", "f32", 5): 4.062e6,
-    ("distributor-1024x512-L3", "f32", 1): 3.573e6,
+    ("distributor-1024x512-L3", "f32", 5): 3.852e6,
+    ("distributor-1024x512-L3", "f32", 1): 3.382e6,
     ("distributor-1024x512-L3", "f32", 0): 3.226e6,
     ("distributor-1024x512-L3", "f64", 3): 4.081e6,
-    ("distributor-1024x512-L3", "f64", 1): 1.927e6,
+    ("distributor-1024x512-L3", "f64", 1): 1.822e6,
     ("distributor-1024x512-L3", "f64", 0): 1.839e6,
-    ("channel-1024x512", "f32", 4): 8.234e6,
+    ("channel-1024x512", "f32", 4): 8.059e6,
     ("channel-1024x512", "f32", 3): 9.328e6,
-    ("channel-1024x512", "f32", 1): 15.39e6,
+    ("channel-1024x512", "f32", 1): 14.81e6,
     ("channel-1024x512", "f32", 0): 16.19e6,
-    ("channel-1024x512", "f32", 5): 19.60e6,
+    ("channel-1024x512", "f32", 5): 18.83e6,
 }
 # The same for the batched kernel, per launch, keyed by (workload, storage,
 # shape, order) like MEASURED_TRAFFIC_PER_LAUNCH.
 MEASURED_VALU_PER_LAUNCH = {
-    ("batch-256-candidates", "f32", 4, 1): 206.5e6,
-    ("batch-256-candidates", "f32", 4, 0): 206.5e6,
-    ("batch-256-candidates", "f32", 3, 1): 199.2e6,
-    ("batch-256-candidates", "f32", 3, 0): 199.2e6,
-    ("batch-256-candidates", "f32", 2, 1): 158.7e6,
-    ("batch-256-candidates", "f32", 1, 1): 385.6e6,
-    ("batch-256-candidates", "f32", 1, 0): 385.6e6,
-    ("batch-256-candidates", "f32", 0, 1): 330.9e6,
-    ("batch-256-candidates", "f32", 0, 0): 330.9e6,
-    ("batch-256-candidates", "f32", 6, 1): 43.54e6,
-    ("batch-256-candidates", "f32", 6, 0): 43.54e6,
+    ("batch-256-candidates", "f32", 4, 1): 204.2e6,
+    ("batch-256-candidates", "f32", 4, 0): 204.2e6,
+    ("batch-256-candidates", "f32", 3, 1): 199.1e6,
+    ("batch-256-candidates", "f32", 3, 0): 199.1e6,
+    ("batch-256-candidates", "f32", 2, 1): 158.5e6,
+    ("batch-256-candidates", "f32", 1, 1): 376.4e6,
+    ("batch-256-candidates", "f32", 1, 0): 376.4e6,
+    ("batch-256-candidates", "f32", 0, 1): 331.4e6,
+    ("batch-256-candidates", "f32", 0, 0): 331.4e6,
+    ("batch-256-candidates", "f32", 6, 1): 41.54e6,
+    ("batch-256-candidates", "f32", 6, 0): 41.54e6,
 }
 VALU_PEAK_WAVE_INSTR_PER_S = 256 * 4 * 2.4e9 / 4
 # What the SIMDs issue at best, measured: 2.3 cycles an FP32 instruction, 4.6 an
