@@ -229,10 +229,11 @@ hipError_t launch_step_batch(const SweepArgs<T> *args, const int32_t *lat,
 // The marching sweep (lbm_march.h, lbm_march_plan.h) on lattices of at least
 // two strips without boundary-variant flags.
 // Waves per SIMD a marching kernel is compiled for: what its registers (12 a
-// step and about 70, twice as many in double) leave of 512.
+// step and about 70, twice as many in double) leave of 512, and at least the
+// two that every plan counts on (march_fill).
 constexpr int march_waves(int steps, size_t arith_bytes, bool check) {
     const int regs = (12 * steps + 70) * (int)(arith_bytes / 4) + (check ? 24 : 0);
-    return regs <= 128 ? 4 : regs <= 168 ? 3 : regs <= 256 ? 2 : 1;
+    return regs <= 128 ? 4 : regs <= 168 ? 3 : 2;
 }
 template <typename T>
 hipError_t launch_march(const SweepArgs<T> &a, const MarchPlan &p, bool check, hipStream_t s);

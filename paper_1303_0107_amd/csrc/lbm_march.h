@@ -14,10 +14,10 @@
 // What it costs beyond the cell update: six lane shifts per cell, the halo
 // lanes (S of 64 on each side) and the rows S - s beyond both ends of the
 // segment that step s also has to advance.  The blocked sweep pays for its
-// two barriers a step, 18 LDS accesses a cell and a halo on regions of 16 or
-// 32 rows; it remains the better one where most cells are solid, since it
-// skips the tiles and rows without fluid and shares one region's work among
-// sixteen waves.
+// barrier a step (two in place), 16 LDS accesses a cell and a halo on regions
+// of 16 or 32 rows; it remains the better one where many cells are solid,
+// since it skips the tiles and rows without fluid and shares one region's work
+// among sixteen waves.  Which lattices march: march_rule (lbm_march_plan.h).
 //
 // The cells' arithmetic is the shared Cell policy on the same operands, so
 // the populations have the bits of one launch per step.
